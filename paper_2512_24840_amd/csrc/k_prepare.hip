@@ -19,18 +19,15 @@ __global__ __launch_bounds__(BLOCK) void k_prepare(Geometry g, State s, const fl
                                                    double bhi1, double bhi2, double bhi3,
                                                    double bhi4, float quantile, int init_state,
                                                    int target_steps) {
-  // the row's (o/w, W w^2) pairs by pixel; before that the keys of a select
   __shared__ __align__(16) float2 stage[kNPL * BLOCK];
   __shared__ uint32_t scratch[kPrepScratch];
   const int spec = blockIdx.x;
   const int tid = threadIdx.x;
   const size_t row = (size_t)spec * g.P;
   float o[kNPL], iv[kNPL];
-  const RowInfo r = prepare_row<BLOCK>(obs + row, ivar + row, g.P, quantile,
-                                       reinterpret_cast<uint32_t *>(stage), scratch, o, iv);
+  const RowInfo r = prepare_row<BLOCK>(obs + row, ivar + row, g.P, quantile, scratch, o, iv);
   const float inv_w = 1.f / r.w;
   const float w2 = r.w * r.w;
-  __syncthreads();  // the keys are no longer read
 #pragma unroll
   for (int i = 0; i < kNPL; ++i) stage[tid + i * BLOCK] = make_float2(o[i] * inv_w, iv[i] * w2);
   __syncthreads();
@@ -62,14 +59,6 @@ __global__ __launch_bounds__(BLOCK) void k_prepare(Geometry g, State s, const fl
       if (s.nrise) s.nrise[spec] = 0;
     }
   }
-}
-
-// OUT_OF_BOX of the parameters u (|u_t| > 1.5 for some t, or not finite).
-__device__ inline uint32_t box_bit(const float *u) {
-  uint32_t b = 0;
-  for (int t = 0; t < kNP; ++t)
-    if (!(fabsf(u[t]) <= 1.5f)) b = kStOutOfBox;
-  return b;
 }
 
 // Physical parameters, status and chi2 at the end of a fit.  OUT_OF_BOX is
@@ -169,32 +158,7 @@ __global__ void k_progress(Geometry g, State s, int32_t *steps, int32_t *done) {
   if (done) done[spec] = (s.target && t >= s.target[spec]) ? 1 : 0;
 }
 
-// Per-spectrum results of a forward evaluation: chi2, the objective
-// J = chi2 / n_eff of Eq. 9 (read per spectrum), n_eff and status (with
-// OUT_OF_BOX of the evaluated u).
-__global__ void k_outputs(Geometry g, State s, double *chi2_out, float *J_out, int32_t *neff_out,
-                          uint32_t *status_out) {
-  const int spec = blockIdx.x * blockDim.x + threadIdx.x;
-  if (spec >= g.B) return;
-  const double c = s.chi2[spec];
-  const int n = s.neff[spec];
-  const uint32_t st = (s.status[spec] & ~kStOutOfBox) | box_bit(s.u + (size_t)spec * kNP);
-  s.status[spec] = st;
-  if (chi2_out) chi2_out[spec] = c;
-  if (J_out) J_out[spec] = n > 0 ? (float)(c / (double)n) : 0.f;
-  if (neff_out) neff_out[spec] = n;
-  if (status_out) status_out[spec] = st;
-}
-
 }  // namespace
-
-hipError_t launch_outputs(const Geometry &g, const State &s, double *chi2_out, float *J_out,
-                          int32_t *neff_out, uint32_t *status_out, hipStream_t st) {
-  const int bs = 256;
-  hipLaunchKernelGGL(k_outputs, dim3((g.B + bs - 1) / bs), dim3(bs), 0, st, g, s, chi2_out, J_out,
-                     neff_out, status_out);
-  return hipGetLastError();
-}
 
 hipError_t launch_prepare(const Geometry &g, const State &s, const float *obs, const float *ivar,
                           const float *init_params, const double *lo, const double *hi,

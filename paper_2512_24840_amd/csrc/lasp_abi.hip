@@ -428,7 +428,9 @@ constexpr int kLmCheckEvery = 4;
   } while (0)
 
 // Launch sequence of a forward evaluation at fixed u on the buffers of s
-// (fp rows: 4 when the Jacobian or covariance is wanted, else 1).
+// (fp rows: 4 when the Jacobian or covariance is wanted, else 1).  The
+// kernels read u and write chi2, n_eff and the status where the caller wants
+// them; nothing is copied.
 int forward_enqueue(const Geometry &g, State s, const float *obs, const float *ivar,
                     const float *basis, const float *u, float *out_model, double *out_chi2,
                     float *out_J, int32_t *out_neff, float *out_grad, float *out_jac,
@@ -436,17 +438,23 @@ int forward_enqueue(const Geometry &g, State s, const float *obs, const float *i
   hipStream_t st = (hipStream_t)opts->stream;
   const bool rows4 = out_jac || out_cov;
   s.target = nullptr;
+  const size_t B = (size_t)g.B, P = (size_t)g.P, u_bytes = B * lasp::kNP * sizeof(float);
+  auto over_u = [&](const void *p, size_t bytes) {
+    const char *a = (const char *)p, *b = (const char *)u;
+    return p && a < b + u_bytes && b < a + bytes;
+  };
+  if (over_u(out_model, 4 * B * P) || over_u(out_chi2, 8 * B) || over_u(out_J, 4 * B) ||
+      over_u(out_neff, 4 * B) || over_u(out_grad, u_bytes) || over_u(out_jac, 20 * B * P) ||
+      over_u(out_cov, 200 * B) || over_u(opts->status, 4 * B))  // an output takes u's place
+    LASP_CHECK(hipMemcpyAsync(s.u, u, u_bytes, hipMemcpyDeviceToDevice, st), "copy u");
+  else
+    s.u = const_cast<float *>(u);  // no kernel below takes a step
+  s.chi2 = out_chi2;
+  if (out_neff) s.neff = out_neff;
+  if (opts->status) s.status = opts->status;
   const int bf16 = opts->precision == LASP_PREC_BF16X3;
   int rc = copy_basis(g, s, basis, bf16, st);
   if (rc) return rc;
-  {
-    LASP_TIMED(LASP_K_PREPARE, st);
-    LASP_CHECK(lasp::launch_prepare(g, s, obs, ivar, nullptr, opts->box_lo, opts->box_hi,
-                                    opts->weight_quantile, 0, 0, st),
-               "prepare");
-  }
-  LASP_CHECK(hipMemcpyAsync(s.u, u, sizeof(float) * lasp::kNP * g.B, hipMemcpyDeviceToDevice, st),
-             "copy u");
   s.fp_stride = rows4 ? 4 * g.ldF : g.ldF;
   {
     LASP_TIMED(LASP_K_INTERP_FWD, st);
@@ -454,7 +462,8 @@ int forward_enqueue(const Geometry &g, State s, const float *obs, const float *i
   }
   {
     LASP_TIMED(LASP_K_FUSED, st);
-    LASP_CHECK(lasp::launch_fused(g, s, out_grad ? 1 : 0, out_model, 1, st), "fused pass");
+    const lasp::OneShot os{obs, ivar, opts->weight_quantile, rows4 ? 1 : 0, out_J};
+    LASP_CHECK(lasp::launch_fused_oneshot(g, s, out_grad ? 1 : 0, out_model, os, st), "fused pass");
   }
   if (out_grad) {
     LASP_TIMED(LASP_K_INTERP_BWD, st);
@@ -465,7 +474,6 @@ int forward_enqueue(const Geometry &g, State s, const float *obs, const float *i
     LASP_CHECK(lasp::launch_cov(g, s, opts->box_lo, opts->box_hi, out_cov, out_jac, nullptr, nullptr, st),
                "covariance / model Jacobian");
   }
-  LASP_CHECK(lasp::launch_outputs(g, s, out_chi2, out_J, out_neff, opts->status, st), "outputs");
   return LASP_OK;
 }
 

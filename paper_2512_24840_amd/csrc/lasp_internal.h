@@ -124,6 +124,16 @@ struct CleanArgs {
   State s;             // ow, wscale, neff, t, target (others unused)
 };
 
+// Inputs and outputs of a one-shot evaluation's fused pass, which prepares
+// its spectra itself.
+struct OneShot {
+  const float *obs;   // [B][P]
+  const float *ivar;  // [B][P]
+  float quantile;     // of the flux weight
+  int write_ow;       // 1: leave (o/w, W w^2) in s.ow for a later kernel
+  float *J;           // optional [B]
+};
+
 struct AdamCfg {
   float lr, beta1, beta2, eps;
   int stop_window;  // 0: fixed step count
@@ -159,6 +169,11 @@ hipError_t launch_interp_fwd(const Geometry &g, const State &s, int deriv_rows, 
 // steps (status untouched).
 hipError_t launch_fused(const Geometry &g, const State &s, int adjoint, float *model_out,
                         int set_status, hipStream_t st);
+// The same pass with the preparation of each spectrum in it, for an
+// evaluation at fixed parameters: writes chi2, n_eff, the flux weight and the
+// whole status.
+hipError_t launch_fused_oneshot(const Geometry &g, const State &s, int adjoint, float *model_out,
+                                const OneShot &os, hipStream_t st);
 hipError_t launch_interp_bwd(const Geometry &g, const State &s, const AdamCfg *adam,
                              float *grad_out, int bf16x3, hipStream_t st);
 hipError_t launch_split_basis(const Geometry &g, const State &s, hipStream_t st);
@@ -173,8 +188,6 @@ hipError_t launch_progress(const Geometry &g, const State &s, int32_t *steps, in
 hipError_t launch_cov(const Geometry &g, const State &s, const double *box_lo, const double *box_hi,
                       double *out_cov, float *out_jac, double *out_normal, const int *active,
                       hipStream_t st);
-hipError_t launch_outputs(const Geometry &g, const State &s, double *chi2_out, float *J_out,
-                          int32_t *neff_out, uint32_t *status_out, hipStream_t st);
 hipError_t launch_lm_init(const Geometry &g, const LmState &lm, hipStream_t st);
 hipError_t launch_lm_solve(const Geometry &g, const State &s, const LmState &lm, hipStream_t st);
 hipError_t launch_lm_active(const Geometry &g, const LmState &lm, hipStream_t st);
@@ -191,6 +204,14 @@ size_t fused_smem_bytes(const Geometry &g);
 
 // -------------------------------------------------------------- device side
 #ifdef __HIPCC__
+
+// OUT_OF_BOX of the parameters u (|u_t| > 1.5 for some t, or not finite).
+__device__ inline uint32_t box_bit(const float *u) {
+  uint32_t b = 0;
+  for (int t = 0; t < kNP; ++t)
+    if (!(fabsf(u[t]) <= 1.5f)) b = kStOutOfBox;
+  return b;
+}
 
 // Eq. 1 features: monomials of total degree <= 3 in x = (u1, u2, u3),
 // graded lexicographic order.

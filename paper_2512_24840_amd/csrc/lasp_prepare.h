@@ -7,10 +7,6 @@
 
 namespace lasp {
 
-__device__ inline bool pixel_ok(float o, float iv) {
-  return isfinite(o) && isfinite(iv) && iv > 0.f;
-}
-
 // Order-preserving map of a float to an unsigned key.
 __device__ inline uint32_t fkey(float f) {
   uint32_t b = __float_as_uint(f);
@@ -24,103 +20,9 @@ __device__ inline float funkey(uint32_t k) {
 // Key of a pixel left out of the selection (no finite flux maps to it).
 constexpr uint32_t kNoKey = 0xffffffffu;
 
-// Scratch of the preparation in LDS: 256 counters, then the reductions.
-constexpr int kPrepScratch = 256 + 2 + 8 + 3 * 8;  // 32-bit words
-
-// k-th smallest (0-based) flux among the valid pixels of one spectrum, by a
-// four-pass 8-bit radix select over the order-preserving keys (in LDS,
-// kNoKey for invalid pixels).  Each pass counts the candidates' digits into
-// 256 bins (a wave whose candidates all share one digit adds them with one
-// atomic), then every thread takes its bins in a block-wide prefix sum and
-// the one thread whose bin holds the k-th candidate records the digit and
-// the rank within it.
-template <int BLOCK>
-__device__ float block_select(const uint32_t *keys, int P, uint32_t k, uint32_t *hist,
-                              uint32_t *sh) {
-  constexpr int kOwn = BLOCK >= 256 ? 1 : 256 / BLOCK;  // bins per thread (threads past 256: none)
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  uint32_t *wsum = sh + 2;  // [BLOCK / 64] totals of each wave's bins
-  uint32_t prefix = 0, mask = 0;
-  for (int shift = 24; shift >= 0; shift -= 8) {
-    for (int b = tid; b < 256; b += BLOCK) hist[b] = 0;
-    __syncthreads();
-    for (int j = tid; j < P; j += BLOCK) {
-      const uint32_t key = keys[j];
-      const bool take = key != kNoKey && (key & mask) == prefix;
-      const uint32_t bin = (key >> shift) & 255u;
-      const uint64_t tk = __ballot(take);
-      if (tk == 0) continue;
-      const int first = __ffsll((unsigned long long)tk) - 1;
-      const uint32_t b0 = __shfl(bin, first);
-      if (__ballot(take && bin == b0) == tk) {
-        if (lane == first) atomicAdd(&hist[b0], (uint32_t)__popcll(tk));
-      } else if (take) {
-        atomicAdd(&hist[bin], 1u);
-      }
-    }
-    __syncthreads();
-    uint32_t h[kOwn], mine = 0;
-#pragma unroll
-    for (int q = 0; q < kOwn; ++q) {
-      h[q] = tid * kOwn + q < 256 ? hist[tid * kOwn + q] : 0u;
-      mine += h[q];
-    }
-    uint32_t incl = mine;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const uint32_t y = __shfl_up(incl, o);
-      if (lane >= o) incl += y;
-    }
-    if (lane == 63) wsum[wave] = incl;
-    __syncthreads();
-    for (int w = 0; w < wave; ++w) incl += wsum[w];
-    uint32_t below = incl - mine;
-    // bins 0..254 hold the k-th candidate when below <= k < below + h; bin
-    // 255 takes whatever rank is past bin 254
-#pragma unroll
-    for (int q = 0; q < kOwn; ++q) {
-      const int bin = tid * kOwn + q;
-      if (bin < 256 && below <= k && (bin == 255 || k < below + h[q])) {
-        sh[0] = (uint32_t)bin;
-        sh[1] = k - below;
-      }
-      below += h[q];
-    }
-    __syncthreads();
-    prefix |= sh[0] << shift;
-    mask |= 255u << shift;
-    k = sh[1];
-    __syncthreads();
-  }
-  return funkey(prefix);
-}
-
-// The (k+1)-th smallest valid flux right after block_select(k) returned key0
-// (its last pass left the digit and the rank in sh[0], sh[1] and the count of
-// that exact key in hist): key0 again if another pixel holds it, else the
-// smallest valid key above key0.
-template <int BLOCK>
-__device__ float block_select_next(const uint32_t *keys, int P, uint32_t key0,
-                                   const uint32_t *hist, uint32_t *sh) {
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  uint32_t *wmin = sh + 2;  // [BLOCK / 64]
-  if (sh[1] + 1 < hist[sh[0]]) return funkey(key0);  // block uniform
-  uint32_t m = kNoKey;  // above every valid key
-  for (int j = tid; j < P; j += BLOCK) {
-    const uint32_t key = keys[j];
-    if (key > key0) m = min(m, key);
-  }
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) m = min(m, (uint32_t)__shfl_xor(m, o));
-  __syncthreads();  // every thread has read sh and hist
-  if (lane == 0) wmin[wave] = m;
-  __syncthreads();
-  m = wmin[0];
-#pragma unroll
-  for (int w = 1; w < BLOCK / 64; ++w) m = min(m, wmin[w]);
-  __syncthreads();
-  return funkey(m);
-}
+// Scratch of the preparation in LDS, 32-bit words: two sets of per-wave
+// partial results, used in turn, so that one barrier serves each sum.
+constexpr int kPrepScratch = 3 * 8;
 
 // What the preparation finds out about one spectrum.
 struct RowInfo {
@@ -141,59 +43,65 @@ struct RowInfo {
 // of their value, show that both order statistics next to the quantile, and
 // with them q, lie inside it; then w = 2^b whatever q is.  b starts from the
 // mean flux and moves by one towards the quantile, which takes one or two
-// counts over registers (two compares and two scalar population counts per
-// pixel) on a spectrum.  Where the bracket does not close -- order
-// statistics on both sides of an end or within 2^-12 of it, nonpositive or
-// widely scattered fluxes -- q is formed from the order statistics of a
-// radix select over keys in LDS (`keys`, P words).
+// counts over registers (four operations per pixel) on a spectrum.  Where
+// the bracket does not close -- order statistics on both sides of an end or
+// within 2^-12 of it, nonpositive or widely scattered fluxes -- q is formed
+// from the order statistics themselves, found bit by bit by the same kind of
+// counts over order-preserving keys.
 //
 // Every thread of the workgroup gets the same RowInfo.  scratch: kPrepScratch
-// words of LDS; keys and scratch are free again after a barrier.
+// words of LDS, free again after a barrier.
 template <int BLOCK>
 __device__ inline RowInfo prepare_row(const float *o_row, const float *i_row, int P, float quantile,
-                                      uint32_t *keys, uint32_t *scratch, float (&o)[kNPL],
-                                      float (&iv)[kNPL]) {
+                                      uint32_t *scratch, float (&o)[kNPL], float (&iv)[kNPL]) {
   constexpr int NW = BLOCK / 64;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  uint32_t *hist = scratch, *sh = scratch + 256;
-  int *red_n = reinterpret_cast<int *>(scratch + 256 + 2 + 8);  // [3][8]
-  int *red_b = red_n + 8;
-  float *red_s = reinterpret_cast<float *>(red_n + 16);
+  int slot = 0;
+  auto total = [&](int v) {  // sum over the workgroup
+    uint32_t *red = scratch + 8 * slot;
+    slot ^= 1;
+    v = wave_sum(v);
+    if (lane == 0) red[wave] = (uint32_t)v;
+    __syncthreads();
+    int t = 0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) t += (int)red[w];
+    return __builtin_amdgcn_readfirstlane(t);
+  };
 #pragma unroll
   for (int i = 0; i < kNPL; ++i) {
-    const int j = tid + i * BLOCK;
-    o[i] = j < P ? o_row[j] : 0.f;
-    iv[i] = j < P ? i_row[j] : 0.f;
+    const int j = min(tid + i * BLOCK, P - 1);
+    o[i] = o_row[j];
+    iv[i] = i_row[j];
   }
   int n = 0;
-  uint64_t bad = 0;
-  float sum = 0.f;
+  float sum = 0.f, fin = 0.f;  // fin: NaN once a value is not finite
 #pragma unroll
   for (int i = 0; i < kNPL; ++i) {
-    bad |= __ballot(!isfinite(o[i]) || !isfinite(iv[i]));
-    const bool ok = pixel_ok(o[i], iv[i]);
-    n += __popcll(__ballot(ok));
-    o[i] = ok ? o[i] : 0.f;
+    fin = fmaf(o[i], 0.f, fmaf(iv[i], 0.f, fin));
+    const bool ok = isfinite(o[i]) && isfinite(iv[i]) && iv[i] > 0.f && tid + i * BLOCK < P;
+    n += ok ? 1 : 0;
+    sum += ok ? o[i] : 0.f;
+    o[i] = ok ? o[i] : INFINITY;  // above every valid flux in the counts
     iv[i] = ok ? iv[i] : 0.f;
-    sum += o[i];
   }
-  sum = wave_sum(sum);
-  if (lane == 0) {
-    red_n[wave] = n;
-    red_b[wave] = bad != 0 ? 1 : 0;
-    red_s[wave] = sum;
-  }
-  __syncthreads();
   RowInfo r{0, 0, 1.f};
+  sum = wave_sum(sum);
+  if (lane == 0) scratch[16 + wave] = __float_as_uint(sum);
+  n = total(n | (fin != fin ? 1 << 16 : 0));  // at most 8,704 pixels, 512 flags
+  r.n_eff = n & 0xffff;
+  r.any_bad = n >> 16 != 0 ? 1u : 0u;
   sum = 0.f;
 #pragma unroll
-  for (int w = 0; w < NW; ++w) {
-    r.n_eff += red_n[w];
-    r.any_bad |= (uint32_t)red_b[w];
-    sum += red_s[w];
+  for (int w = 0; w < NW; ++w) sum += __uint_as_float(scratch[16 + w]);
+  auto clear = [&]() {
+#pragma unroll
+    for (int i = 0; i < kNPL; ++i) o[i] = iv[i] > 0.f ? o[i] : 0.f;
+  };
+  if (!(quantile > 0.f) || r.n_eff == 0) {
+    clear();
+    return r;
   }
-  r.n_eff = __builtin_amdgcn_readfirstlane(r.n_eff);
-  if (!(quantile > 0.f) || r.n_eff == 0) return r;
 
   const float pos = quantile * (float)(r.n_eff - 1);
   const uint32_t k0 = (uint32_t)floorf(pos);
@@ -212,53 +120,64 @@ __device__ inline RowInfo prepare_row(const float *o_row, const float *i_row, in
       int c_lo = 0, c_hi = 0;
 #pragma unroll
       for (int i = 0; i < kNPL; ++i) {
-        const float x = iv[i] > 0.f ? o[i] : INFINITY;
-        c_lo += __popcll(__ballot(x < lo));
-        c_hi += __popcll(__ballot(x <= hi));
+        c_lo += o[i] < lo ? 1 : 0;
+        c_hi += o[i] <= hi ? 1 : 0;
       }
-      __syncthreads();  // the previous counts have been read
-      if (lane == 0) {
-        red_n[wave] = c_lo;
-        red_b[wave] = c_hi;
-      }
-      __syncthreads();
-      c_lo = c_hi = 0;
-#pragma unroll
-      for (int q = 0; q < NW; ++q) {
-        c_lo += red_n[q];
-        c_hi += red_b[q];
-      }
-      c_lo = __builtin_amdgcn_readfirstlane(c_lo);
-      c_hi = __builtin_amdgcn_readfirstlane(c_hi);
-      if ((uint32_t)c_lo <= k0 && k1 < (uint32_t)c_hi) {
+      const uint32_t c = (uint32_t)total(c_lo | c_hi << 16);
+      if ((c & 0xffffu) <= k0 && k1 < c >> 16) {
         w = exp2f((float)b);
         found = true;
         break;
       }
-      const int step = k0 < (uint32_t)c_lo ? -1 : 1;
+      const int step = k0 < (c & 0xffffu) ? -1 : 1;
       go = dir == 0 || step == dir;  // past the quantile: the ends part it
       dir = step;
       b += step;
     }
   }
   if (!found) {
-    __syncthreads();
+    // keys in place of the fluxes; the k0-th smallest is the largest value
+    // that at most k0 keys are below
+    uint32_t kth = 0;
 #pragma unroll
-    for (int i = 0; i < kNPL; ++i) {
-      const int j = tid + i * BLOCK;
-      if (j < P) keys[j] = iv[i] > 0.f ? fkey(o[i]) : kNoKey;
+    for (int i = 0; i < kNPL; ++i) o[i] = __uint_as_float(iv[i] > 0.f ? fkey(o[i]) : kNoKey);
+#pragma unroll 1
+    for (uint32_t bit = 0x80000000u; bit != 0; bit >>= 1) {
+      const uint32_t t = kth | bit;
+      int c = 0;
+#pragma unroll
+      for (int i = 0; i < kNPL; ++i) c += __float_as_uint(o[i]) < t ? 1 : 0;
+      if ((uint32_t)total(c) <= k0) kth = t;
     }
-    __syncthreads();
-    const float v0 = block_select<BLOCK>(keys, P, k0, hist, sh);
+    const float v0 = funkey(kth);
     float q = v0;
     if (k1 > k0) {
-      const float v1 = block_select_next<BLOCK>(keys, P, fkey(v0), hist, sh);
+      // the next one: the same key if another pixel holds it, else the
+      // smallest above it
+      int c = 0;
+      uint32_t m = kNoKey;
+#pragma unroll
+      for (int i = 0; i < kNPL; ++i) {
+        const uint32_t key = __float_as_uint(o[i]);
+        c += key <= kth ? 1 : 0;
+        m = key > kth ? min(m, key) : m;
+      }
+#pragma unroll
+      for (int s = 32; s > 0; s >>= 1) m = min(m, (uint32_t)__shfl_xor(m, s));
+      if (lane == 0) scratch[16 + wave] = m;  // the mean's partials have been read
+      const uint32_t upto = (uint32_t)total(c);
+#pragma unroll
+      for (int v = 0; v < NW; ++v) m = min(m, scratch[16 + v]);
+      const float v1 = k1 < upto ? v0 : funkey(m);
       q = v0 + frac * (v1 - v0);
     }
     if (q > 0.f && isfinite(q)) w = exp2f(rintf(log2f(q)));
+#pragma unroll
+    for (int i = 0; i < kNPL; ++i) o[i] = funkey(__float_as_uint(o[i]));
   }
   if (!(w > 0.f) || !isfinite(w) || !isfinite(1.f / (w * w))) w = 1.f;
   r.w = w;
+  clear();
   return r;
 }
 
