@@ -26,13 +26,18 @@
 // in LDS once F' has been read for the last time.
 #include <type_traits>
 
+#include "lasp_continuum.h"
 #include "lasp_prepare.h"
+
+// Every fused multiply-add below is written out: the compiler then forms none
+// of its own, and the pass gives the same bits in each of its variants (a
+// step, an evaluation of the returned point, a one-shot evaluation).
+#pragma clang fp contract(off)
 
 namespace lasp {
 namespace {
 
 constexpr int kOffF = 16;  // F' column c lives at sF[kOffF + c]
-constexpr int kMid = kNPL / 2;  // each lane expands the continuum about its pixel j0 + kMid
 
 // [x^n] T_k(x) for k, n <= 10, from T_k = 2x T_{k-1} - T_{k-2}.
 struct ChebPow {
@@ -113,13 +118,16 @@ __host__ __device__ inline FusedLayout fused_layout(const Geometry &g, int nwave
 // and read once, 69.6 KB of the 117 KB that one spectrum then moves, beside a
 // launch of its own.  Measured at 65,536 x 3,900, preparation and pass:
 // 1.78 ms, against 0.80 + 1.45 ms with k_prepare before it.
-template <int BLOCK, int ND, bool ADJ, bool MULTI, bool ONESHOT>
+// NODES: the continuum moments by nodes (moment_nodes_hold); always where the
+// workgroup has more than 128 threads, as such rows have over 2,000 pixels.
+template <int BLOCK, int ND, bool ADJ, bool MULTI, bool ONESHOT, bool NODES>
 __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(4))) void k_fused(
     Geometry g, State s, float *model_out, int set_status, OneShot os) {
   constexpr int NW = BLOCK / 64;
   constexpr int NNU = 2 * ND - 1;  // nu_0 .. nu_{2D}
   constexpr int NMOM = NNU + ND;   // plus r_0 .. r_D
   constexpr int NWIN = kNPL + kTB - 1;
+  constexpr bool kStep = ADJ && !ONESHOT;  // the pass of an Adam step: no status, no model
   extern __shared__ __align__(16) unsigned char smem[];
   const FusedLayout L = fused_layout(g, NW, NMOM);
   float *sF = reinterpret_cast<float *>(smem);  // region A
@@ -304,54 +312,20 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(4))) void
   }
 
   // ---- Eq. 6 moments: nu_l = sum W F''^2 T_l (l <= 2D), r_n = sum W F'' o T_n
-  //      (n <= D), in one pass over the lane's pixels with T_0 .. T_D only:
-  //      T_{D+k} = 2 T_D T_k - T_{D-k}, so nu_{D+k} = 2 q_k - nu_{D-k} with
-  //      q_k = sum W F''^2 T_D T_k (k = 1..D).  Each lane sums its 17 pixels
-  //      in FP32, eight lanes' sums are added in FP32 on their way through
-  //      LDS; the sums over those groups and the waves, the combination and
-  //      the solve are FP64.
+  //      (n <= D), from T_0 .. T_D only: T_{D+k} = 2 T_D T_k - T_{D-k}, so
+  //      nu_{D+k} = 2 q_k - nu_{D-k} with q_k = sum W F''^2 T_D T_k (k =
+  //      1..D).  Each lane folds its 17 pixels onto seven nodes where
+  //      those hold the polynomials (NODES) and sums in FP32, eight lanes' sums are added in
+  //      FP32 on their way through LDS; the sums over those groups and the
+  //      waves, the combination and the solve are FP64.
   {
-    const float two_over_p = 2.f / (float)P;
-    const float x0 = fmaf((float)j0, two_over_p, -1.f);
 #pragma unroll
     for (int i = 0; i < kNPL; ++i) {
       opaque(fpp[i]);
       opaque(ow[i]);
     }
-    float nu[ND], q[ND], rr[ND];  // nu_0..nu_D, q_1..q_D (q[0] unused), r_0..r_D
-#pragma unroll
-    for (int k = 0; k < ND; ++k) nu[k] = q[k] = rr[k] = 0.f;
-#pragma unroll
-    for (int i = 0; i < kNPL; ++i) {
-      const float x = fmaf((float)i, two_over_p, x0);
-      const float wf = ow[i].y * fpp[i];
-      const float y = wf * fpp[i];   // W F''^2
-      const float z = wf * ow[i].x;  // W F'' o
-      const float x2 = x + x;
-      float t[ND];  // T_0(x) .. T_D(x)
-      t[0] = 1.f;
-      t[1] = x;
-#pragma unroll
-      for (int l = 2; l < ND; ++l) t[l] = fmaf(x2, t[l - 1], -t[l - 2]);
-      const float yd = y * t[ND - 1];
-      nu[0] += y;
-      rr[0] += z;
-#pragma unroll
-      for (int l = 1; l < ND; ++l) {
-        nu[l] = fmaf(y, t[l], nu[l]);
-        q[l] = fmaf(yd, t[l], q[l]);
-        rr[l] = fmaf(z, t[l], rr[l]);
-      }
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    // lane partials in the order nu_0..nu_D, q_1..q_D, r_0..r_D
     float acc[NMOM];
-#pragma unroll
-    for (int k = 0; k < ND; ++k) acc[k] = nu[k];
-#pragma unroll
-    for (int k = 1; k < ND; ++k) acc[ND - 1 + k] = q[k];
-#pragma unroll
-    for (int k = 0; k < ND; ++k) acc[NNU + k] = rr[k];
+    lane_moments<NODES, ND>(j0, P, fpp, ow, acc);
     block_sum_lds_f32<NW, NMOM>(acc, sB, sRed, sMom, lane, wave);
   }
 
@@ -436,7 +410,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(4))) void
   const bool ok = __builtin_amdgcn_readfirstlane((int)(sScal[0] != 0.0)) != 0;
   const int n_eff = ONESHOT ? row.n_eff : s.neff[spec];
   const float gscale = n_eff > 0 ? -2.f / (float)n_eff : 0.f;
-  const float wsc = ONESHOT ? row.w : s.wscale[spec];
+  [[maybe_unused]] const float wsc = ONESHOT ? row.w : s.wscale[spec];
   float gb[kNPL];
   float chi2_part = 0.f;  // this lane's 17 terms; lanes and waves add in FP64
   float cmin = INFINITY;
@@ -444,38 +418,43 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(4))) void
     // Taylor coefficients of t -> C(x_{j0 + kMid} + h t): the series in v
     // shifted to v0 = j0 + kMid - P/2 by repeated synthetic division (FP64),
     // then evaluated by Horner in FP32 at t = i - kMid, |h t| <= 16 / P.
-    float cf[ND];
+    // Rows of more than 128 lanes have over 2,000 pixels: there the terms past
+    // the sixth add at most 1e-10 of the continuum's largest value (the
+    // seventh derivative of a degree-10 polynomial by Markov's bound).
+    constexpr int NC = BLOCK == 128 ? ND : (ND < 7 ? ND : 7);
+    float cf[NC];
     {
       double a[ND];
 #pragma unroll
       for (int n = 0; n < ND; ++n) a[n] = sBd[n];
       const double v0 = (double)(j0 + kMid) - 0.5 * (double)P;
 #pragma unroll
-      for (int k = 0; k < ND - 1; ++k)
+      for (int k = 0; k < ND - 1 && k < NC; ++k)
 #pragma unroll
         for (int n = ND - 2; n >= k; --n) a[n] = fma(v0, a[n + 1], a[n]);
 #pragma unroll
-      for (int n = 0; n < ND; ++n) cf[n] = (float)a[n];
+      for (int n = 0; n < NC; ++n) cf[n] = (float)a[n];
     }
     auto residual = [&](auto inside) {
 #pragma unroll
       for (int i = 0; i < kNPL; ++i) {
         const int j = j0 + i;
         const float t = (float)(i - kMid);
-        float C = cf[ND - 1];
+        float C = cf[NC - 1];
 #pragma unroll
-        for (int k = ND - 2; k >= 0; --k) C = fmaf(C, t, cf[k]);
-        const float mdl = C * fpp[i];
-        const float e = ow[i].x - mdl;
+        for (int k = NC - 2; k >= 0; --k) C = fmaf(C, t, cf[k]);
+        const float e = fmaf(-C, fpp[i], ow[i].x);
         const float we = ow[i].y * e;
         chi2_part = fmaf(we, e, chi2_part);
         gb[i] = (we * C) * gscale;
-        if constexpr (decltype(inside)::value)
-          cmin = fminf(cmin, C);
-        else
-          cmin = fminf(cmin, j < P ? C : INFINITY);
-        if (model_out != nullptr) {
-          if (j < P) model_out[(size_t)spec * P + j] = mdl * wsc;
+        if constexpr (!kStep) {
+          if constexpr (decltype(inside)::value)
+            cmin = fminf(cmin, C);
+          else
+            cmin = fminf(cmin, j < P ? C : INFINITY);
+          if (model_out != nullptr) {
+            if (j < P) model_out[(size_t)spec * P + j] = (C * fpp[i]) * wsc;
+          }
         }
       }
     };
@@ -492,10 +471,10 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(4))) void
   }
   {
     const double cs = wave_sum((double)chi2_part);
-    const float cm = wave_min(cmin);
-    if (lane == 0) {
-      sRed[wave * 64 + 0] = cs;
-      sRed[wave * 64 + 1] = (double)cm;
+    if (lane == 0) sRed[wave * 64 + 0] = cs;
+    if constexpr (!kStep) {
+      const float cm = wave_min(cmin);
+      if (lane == 0) sRed[wave * 64 + 1] = (double)cm;
     }
   }
   __syncthreads();
@@ -504,10 +483,10 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(4))) void
 #pragma unroll
     for (int w = 0; w < NW; ++w) {
       cs += sRed[w * 64 + 0];
-      cm = fmin(cm, sRed[w * 64 + 1]);
+      if constexpr (!kStep) cm = fmin(cm, sRed[w * 64 + 1]);
     }
     s.chi2[spec] = cs;
-    if (set_status) {
+    if (!kStep && set_status) {
       uint32_t st;
       if constexpr (ONESHOT) {
         st = (row.any_bad ? kStNonfinite : 0u) | (n_eff <= kNP + g.nd ? kStNoData : 0u) |
@@ -607,11 +586,12 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(4))) void
         const double d = (double)(idx - H) - mu;
         const double G = (double)sK[a * L.ks + idx];
         const double R = (double)sRs[a * L.ks + idx];
-        s1 += G * d;
-        s2 += G * d * d;
-        rg += R * G;
-        rgd += R * G * d;
-        rgd2 += R * G * d * d;
+        const double gd = G * d, rgv = R * G;
+        s1 += gd;
+        s2 = fma(gd, d, s2);
+        rg += rgv;
+        rgd = fma(rgv, d, rgd);
+        rgd2 = fma(rgv * d, d, rgd2);
       }
       {
         // region B is free once the lag correlation is done
@@ -692,11 +672,11 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(4))) void
   }
 }
 
-template <int BLOCK, int ND, bool ADJ, bool MULTI, bool ONESHOT>
+template <int BLOCK, int ND, bool ADJ, bool MULTI, bool ONESHOT, bool NODES>
 hipError_t launch_fused_k(const Geometry &g, const State &s, float *model_out, int set_status,
                           const OneShot &os, hipStream_t st) {
   const FusedLayout L = fused_layout(g, BLOCK / 64, 3 * ND - 1);
-  auto k = k_fused<BLOCK, ND, ADJ, MULTI, ONESHOT>;
+  auto k = k_fused<BLOCK, ND, ADJ, MULTI, ONESHOT, NODES>;
   hipError_t e =
       hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize, L.bytes);
   if (e != hipSuccess) return e;
@@ -704,26 +684,37 @@ hipError_t launch_fused_k(const Geometry &g, const State &s, float *model_out, i
   return hipGetLastError();
 }
 
-template <int BLOCK, int ND, bool ONESHOT>
+template <int BLOCK, int ND, bool ONESHOT, bool NODES>
 hipError_t launch_fused_t(const Geometry &g, const State &s, int adjoint, float *model_out,
                           int set_status, const OneShot &os, hipStream_t st) {
-  const bool multi = g.n_arms > 1;
-  if (adjoint)
-    return multi
-               ? launch_fused_k<BLOCK, ND, true, true, ONESHOT>(g, s, model_out, set_status, os, st)
-               : launch_fused_k<BLOCK, ND, true, false, ONESHOT>(g, s, model_out, set_status, os, st);
-  return multi ? launch_fused_k<BLOCK, ND, false, true, ONESHOT>(g, s, model_out, set_status, os, st)
-               : launch_fused_k<BLOCK, ND, false, false, ONESHOT>(g, s, model_out, set_status, os, st);
+  auto go = [&](auto adj, auto multi) {
+    return launch_fused_k<BLOCK, ND, decltype(adj)::value, decltype(multi)::value, ONESHOT, NODES>(
+        g, s, model_out, set_status, os, st);
+  };
+  const std::true_type yes;
+  const std::false_type no;
+  if (g.n_arms > 1) return adjoint ? go(yes, yes) : go(no, yes);
+  return adjoint ? go(yes, no) : go(no, no);
+}
+
+template <int BLOCK, int ND, bool ONESHOT>
+hipError_t launch_fused_n(const Geometry &g, const State &s, int adjoint, float *model_out,
+                          int set_status, const OneShot &os, hipStream_t st) {
+  if constexpr (BLOCK == 128) {
+    if (!moment_nodes_hold(ND, g.P))
+      return launch_fused_t<BLOCK, ND, ONESHOT, false>(g, s, adjoint, model_out, set_status, os, st);
+  }
+  return launch_fused_t<BLOCK, ND, ONESHOT, true>(g, s, adjoint, model_out, set_status, os, st);
 }
 
 template <int BLOCK, bool ONESHOT>
 hipError_t launch_fused_b(const Geometry &g, const State &s, int adjoint, float *model_out,
                           int set_status, const OneShot &os, hipStream_t st) {
   switch (g.nd) {
-    case 5: return launch_fused_t<BLOCK, 5, ONESHOT>(g, s, adjoint, model_out, set_status, os, st);
-    case 7: return launch_fused_t<BLOCK, 7, ONESHOT>(g, s, adjoint, model_out, set_status, os, st);
-    case 9: return launch_fused_t<BLOCK, 9, ONESHOT>(g, s, adjoint, model_out, set_status, os, st);
-    case 11: return launch_fused_t<BLOCK, 11, ONESHOT>(g, s, adjoint, model_out, set_status, os, st);
+    case 5: return launch_fused_n<BLOCK, 5, ONESHOT>(g, s, adjoint, model_out, set_status, os, st);
+    case 7: return launch_fused_n<BLOCK, 7, ONESHOT>(g, s, adjoint, model_out, set_status, os, st);
+    case 9: return launch_fused_n<BLOCK, 9, ONESHOT>(g, s, adjoint, model_out, set_status, os, st);
+    case 11: return launch_fused_n<BLOCK, 11, ONESHOT>(g, s, adjoint, model_out, set_status, os, st);
     default: return hipErrorInvalidValue;
   }
 }

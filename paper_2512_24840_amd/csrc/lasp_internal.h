@@ -167,6 +167,7 @@ hipError_t launch_interp_fwd(const Geometry &g, const State &s, int deriv_rows, 
 // set_status: 1 for a pass at the parameters a call returns (the
 // evaluation bits of the status are replaced), 0 for the passes of the
 // steps (status untouched).
+// An adjoint pass is that of an Adam step: model_out NULL, set_status 0.
 hipError_t launch_fused(const Geometry &g, const State &s, int adjoint, float *model_out,
                         int set_status, hipStream_t st);
 // The same pass with the preparation of each spectrum in it, for an
