@@ -22,15 +22,24 @@ namespace {
 
 constexpr int kMaxDPasses = 20;
 
+// The rows come and the mask goes through LDS in pixel order, so that every
+// access to memory is coalesced (a lane's own 17 pixels would put the 64
+// lanes of each access on 64 cache lines), and a pixel keeps two values in
+// registers: its residual and the excess |eps| - f G that all tests use.
+// Measured at 16,384 x 3,900 (0.83 GB): 0.249 ms, against 0.566 ms with
+// lane-strided accesses and three values per pixel.
 template <int BLOCK>
-__global__ __launch_bounds__(BLOCK) void k_clean(Geometry g, CleanArgs a) {
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(4))) void k_clean(
+    Geometry g, CleanArgs a) {
   constexpr int NW = BLOCK / 64;
+  constexpr int kRow = kNPL * BLOCK;
+  constexpr int kScr = NW * 512 * 2;  // floats of block_sum_lds' scratch
+  __shared__ __align__(16) float sRow[kRow > kScr ? kRow : kScr];
   __shared__ double sRed[NW * 64];
-  __shared__ double sOut[8];
-  __shared__ double sScr[NW * 512];
-  __shared__ double sEL[BLOCK], sER[BLOCK];  // eps of each thread's first and last pixel
-  __shared__ double sML[BLOCK], sMR[BLOCK];  // model of the same pixels
-  __shared__ uint32_t sOL[BLOCK], sOR[BLOCK];  // outlier flag of the same pixels
+  __shared__ double sOut[2];
+  __shared__ int sCnt[2][NW];
+  __shared__ uint32_t sFl[2][BLOCK];  // each thread's flags, two sets used in turn
+  double *sScr = reinterpret_cast<double *>(sRow);
   const int spec = blockIdx.x;
   if (a.s.target && a.s.t[spec] >= a.s.target[spec]) return;  // a stopped fit keeps its mask
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -38,122 +47,130 @@ __global__ __launch_bounds__(BLOCK) void k_clean(Geometry g, CleanArgs a) {
   const int j0 = tid * kNPL;
   const size_t row = (size_t)spec * P;
 
-  double eps[kNPL], m[kNPL];
+  // one row through LDS: the lane's pixels and the two beside them
+  auto fetch = [&](const float *src, float (&v)[kNPL + 2]) {
+    float x[kNPL];
+#pragma unroll
+    for (int i = 0; i < kNPL; ++i) x[i] = src[row + min(tid + i * BLOCK, P - 1)];
+    __syncthreads();  // the previous row has been read
+#pragma unroll
+    for (int i = 0; i < kNPL; ++i) sRow[tid + i * BLOCK] = x[i];
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kNPL; ++i) v[i + 1] = sRow[j0 + i];
+    v[0] = sRow[max(j0 - 1, 0)];
+    v[kNPL + 1] = sRow[min(j0 + kNPL, kRow - 1)];
+  };
+  float m[kNPL + 2], o[kNPL + 2], iv[kNPL + 2];
+  fetch(a.model, m);
+  fetch(a.obs, o);
+  fetch(a.ivar, iv);
+  double eps[kNPL], exc[kNPL];  // residual (0 where invalid), |residual| - f G
+  double el = 0.0, er = 0.0;    // residuals of pixels j0 - 1 and j0 + 17
   uint32_t valid = 0;
-#pragma unroll
-  for (int i = 0; i < kNPL; ++i) {
-    const int j = j0 + i;
-    double e = 0.0, mm = 0.0;
-    if (j < P) {
-      const float o = a.obs[row + j], iv = a.ivar[row + j];
-      mm = (double)a.model[row + j];
-      if (isfinite(o) && isfinite(iv) && iv > 0.f) {
-        valid |= 1u << i;
-        e = (double)o - mm;
-      }
-    }
-    eps[i] = e;
-    m[i] = mm;
-  }
-  sML[tid] = m[0];
-  sMR[tid] = m[kNPL - 1];
-  sEL[tid] = eps[0];
-  sER[tid] = eps[kNPL - 1];
-  __syncthreads();
-  // flux gradient G_j = max(|m_j - m_{j-1}|, |m_j - m_{j+1}|), ends use one side
-  double G[kNPL];
-#pragma unroll
-  for (int i = 0; i < kNPL; ++i) {
-    const int j = j0 + i;
-    const double ml = i > 0 ? m[i - 1] : (tid > 0 ? sMR[tid - 1] : 0.0);
-    const double mr = i < kNPL - 1 ? m[i + 1] : (tid + 1 < BLOCK ? sML[tid + 1] : 0.0);
-    const double gl = j > 0 ? fabs(m[i] - ml) : 0.0;
-    const double gr = j + 1 < P ? fabs(m[i] - mr) : 0.0;
-    G[i] = fmax(gl, gr);
-  }
   const double f = (double)a.f_shift;
+#pragma unroll
+  for (int i = -1; i <= kNPL; ++i) {
+    const int j = j0 + i;
+    const float ov = o[i + 1], wv = iv[i + 1];
+    const bool ok = j >= 0 && j < P && isfinite(ov) && isfinite(wv) && wv > 0.f;
+    const double e = ok ? (double)ov - (double)m[i + 1] : 0.0;
+    if (i < 0) {
+      el = e;
+    } else if (i == kNPL) {
+      er = e;
+    } else {
+      if (ok) valid |= 1u << i;
+      eps[i] = e;
+      // flux gradient G_j = max(|m_j - m_{j-1}|, |m_j - m_{j+1}|), ends use one side
+      const double mj = (double)m[i + 1];
+      const double gl = j > 0 ? fabs(mj - (double)m[i]) : 0.0;
+      const double gr = j + 1 < P ? fabs(mj - (double)m[i + 2]) : 0.0;
+      exc[i] = fma(-f, fmax(gl, gr), fabs(e));
+    }
+  }
 
-  // sample standard deviation of eps over the valid pixels
-  auto stats = [&](uint32_t sel, double &sd, double &n_out) {
-    double acc[2] = {0.0, 0.0};
+  int slot = 0;
+  auto count = [&](uint32_t flags) {  // flagged pixels of the spectrum
+    slot ^= 1;
+    const int c = wave_sum((int)__popc(flags));
+    if (lane == 0) sCnt[slot][wave] = c;
+    __syncthreads();
+    int t = 0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) t += sCnt[slot][w];
+    return t;
+  };
+  // sample standard deviation of eps over the selected pixels
+  auto stats = [&](uint32_t sel, int n) {
+    double acc[1] = {0.0};
 #pragma unroll
     for (int i = 0; i < kNPL; ++i)
-      if (sel >> i & 1u) {
-        acc[0] += 1.0;
-        acc[1] += eps[i];
-      }
-    block_sum_lds<NW, 2>(acc, sScr, sRed, sOut, lane, wave);
-    const double n = sOut[0], mean = n > 0.0 ? sOut[1] / n : 0.0;
+      if (sel >> i & 1u) acc[0] += eps[i];
+    block_sum_lds<NW, 1>(acc, sScr, sRed, sOut, lane, wave);
+    const double mean = n > 0 ? sOut[0] / (double)n : 0.0;
     double v[1] = {0.0};
 #pragma unroll
     for (int i = 0; i < kNPL; ++i)
       if (sel >> i & 1u) v[0] += (eps[i] - mean) * (eps[i] - mean);
-    block_sum_lds<NW, 1>(v, sScr, sRed, sOut + 2, lane, wave);
-    sd = n > 1.0 ? sqrt(sOut[2] / (n - 1.0)) : 0.0;
-    n_out = n;
+    block_sum_lds<NW, 1>(v, sScr, sRed, sOut + 1, lane, wave);
+    return n > 1 ? sqrt(sOut[1] / ((double)n - 1.0)) : 0.0;
   };
-  double sigma, nv;
-  stats(valid, sigma, nv);
+  const int nv = count(valid);  // its barrier also ends the last row's reads
+  const double sigma = stats(valid, nv);
 
-  // B with the relaxed thresholds k = 3, 4, 5, 7 (k is set before each count,
-  // so the last one stands if every count is above 3 %)
-  double k = 3.0;
+  // B with the relaxed thresholds k = 3, 4, 5, 7 (the last one stands if
+  // every count is above 3 %)
+  uint32_t bout = 0;
   for (int q = 0; q < 4; ++q) {
-    k = q == 0 ? 3.0 : (q == 1 ? 4.0 : (q == 2 ? 5.0 : 7.0));
-    double c[1] = {0.0};
+    const double k = q == 0 ? 3.0 : (q == 1 ? 4.0 : (q == 2 ? 5.0 : 7.0));
+    bout = 0;
 #pragma unroll
     for (int i = 0; i < kNPL; ++i)
-      if ((valid >> i & 1u) && fabs(eps[i]) - f * G[i] > k * sigma) c[0] += 1.0;
-    block_sum_lds<NW, 1>(c, sScr, sRed, sOut + 3, lane, wave);
-    if (sOut[3] <= 0.03 * nv) break;
+      if ((valid >> i & 1u) && exc[i] > k * sigma) bout |= 1u << i;
+    if ((double)count(bout) <= 0.03 * (double)nv) break;
   }
-  uint32_t bout = 0;
-#pragma unroll
-  for (int i = 0; i < kNPL; ++i)
-    if ((valid >> i & 1u) && fabs(eps[i]) - f * G[i] > k * sigma) bout |= 1u << i;
 
-  // neighbour flags across thread boundaries
-  auto exchange = [&](uint32_t flags, uint32_t &left, uint32_t &right) {
+  // flags of the pixels beside the lane's, from the neighbouring threads
+  int set = 0;
+  auto beside = [&](uint32_t flags, uint32_t &left, uint32_t &right) {
+    set ^= 1;
+    sFl[set][tid] = flags;
     __syncthreads();
-    sOL[tid] = flags & 1u;
-    sOR[tid] = flags >> (kNPL - 1) & 1u;
-    __syncthreads();
-    left = tid > 0 ? sOR[tid - 1] : 0u;           // flag of pixel j0 - 1
-    right = tid + 1 < BLOCK ? sOL[tid + 1] : 0u;  // flag of pixel j0 + 17
+    left = tid > 0 ? sFl[set][tid - 1] >> (kNPL - 1) & 1u : 0u;
+    right = tid + 1 < BLOCK ? sFl[set][tid + 1] & 1u : 0u;
   };
   uint32_t bl, br;
-  exchange(bout, bl, br);
+  beside(bout, bl, br);
   // C: neighbours of B outliers above 2 sigma
   uint32_t cout = 0;
+  {
+    const uint32_t near = (bout << 1 | bl) | (bout >> 1 | br << (kNPL - 1));
+#pragma unroll
+    for (int i = 0; i < kNPL; ++i)
+      if ((valid & near) >> i & 1u && exc[i] > 2.0 * sigma) cout |= 1u << i;
+  }
+  const uint32_t kept = valid & ~bout & ~cout;
+  const double sigma2 = stats(kept, count(kept));
+
+  // D: grow from the outliers through same-sign, not larger neighbours; the
+  // pixels that may join, by which side
+  uint32_t from_l = 0, from_r = 0;
 #pragma unroll
   for (int i = 0; i < kNPL; ++i) {
-    const bool nb = (i > 0 ? (bout >> (i - 1) & 1u) : bl) || (i < kNPL - 1 ? (bout >> (i + 1) & 1u) : br);
-    if ((valid >> i & 1u) && nb && fabs(eps[i]) - f * G[i] > 2.0 * sigma) cout |= 1u << i;
+    const double es = i > 0 ? eps[i > 0 ? i - 1 : 0] : el;
+    const double et = i < kNPL - 1 ? eps[i < kNPL - 1 ? i + 1 : i] : er;
+    const bool may = (valid >> i & 1u) && exc[i] > sigma2;
+    if (may && es * eps[i] > 0.0 && fabs(eps[i]) <= fabs(es)) from_l |= 1u << i;
+    if (may && et * eps[i] > 0.0 && fabs(eps[i]) <= fabs(et)) from_r |= 1u << i;
   }
-  double sigma2, n2;
-  stats(valid & ~bout & ~cout, sigma2, n2);
-
-  // D: grow from the outliers through same-sign, not larger neighbours
-  const double el = tid > 0 ? sER[tid - 1] : 0.0;           // eps of pixel j0 - 1
-  const double er = tid + 1 < BLOCK ? sEL[tid + 1] : 0.0;  // eps of pixel j0 + 17
   uint32_t dout = 0;
   for (int pass = 0; pass < kMaxDPasses; ++pass) {
-    const uint32_t o = (bout | cout | dout) & valid;
+    const uint32_t out = (bout | cout | dout) & valid;
     uint32_t ol, orr;
-    exchange(o, ol, orr);
-    uint32_t nd = dout;
-#pragma unroll
-    for (int i = 0; i < kNPL; ++i) {
-      if (!(valid >> i & 1u)) continue;
-      const double ae = fabs(eps[i]);
-      if (!(ae - f * G[i] > sigma2)) continue;
-      const bool sl = i > 0 ? (o >> (i - 1) & 1u) : ol;
-      const double es = i > 0 ? eps[i - 1] : el;
-      const bool sr = i < kNPL - 1 ? (o >> (i + 1) & 1u) : orr;
-      const double et = i < kNPL - 1 ? eps[i + 1] : er;
-      if ((sl && es * eps[i] > 0.0 && ae <= fabs(es)) || (sr && et * eps[i] > 0.0 && ae <= fabs(et)))
-        nd |= 1u << i;
-    }
+    beside(out, ol, orr);
+    const uint32_t nd =
+        dout | (from_l & (out << 1 | ol)) | (from_r & (out >> 1 | orr << (kNPL - 1)));
     const int changed = __syncthreads_or(nd != dout);
     dout = nd;
     if (!changed) break;
@@ -161,25 +178,28 @@ __global__ __launch_bounds__(BLOCK) void k_clean(Geometry g, CleanArgs a) {
 
   // outputs: keep flags, the new weights of the fused pass, n_eff
   const uint32_t masked = (bout | cout | dout) & valid;
+  const int n_kept = count(valid & ~masked);
   if (a.keep_out) {
+    uint8_t *sKeep = reinterpret_cast<uint8_t *>(sRow);  // free: the sums above are done
 #pragma unroll
-    for (int i = 0; i < kNPL; ++i)
-      if (j0 + i < P) a.keep_out[row + j0 + i] = (masked >> i & 1u) ? 0 : 1;
+    for (int i = 0; i < kNPL; ++i) sKeep[j0 + i] = (masked >> i & 1u) ? 0 : 1;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kNPL; ++i) {
+      const int j = tid + i * BLOCK;
+      if (j < P) a.keep_out[row + j] = sKeep[j];
+    }
   }
-  double cnt[1] = {(double)__popc(valid & ~masked)};
-  block_sum_lds<NW, 1>(cnt, sScr, sRed, sOut + 4, lane, wave);
   if (a.s.ow) {
     const float w = a.s.wscale[spec];
     const float w2 = w * w;
     float2 *dst = a.s.ow + (size_t)spec * kNPL * BLOCK + tid;
 #pragma unroll
-    for (int i = 0; i < kNPL; ++i) {
-      const int j = j0 + i;
-      if (j < P && (valid >> i & 1u)) dst[i * BLOCK].y = (masked >> i & 1u) ? 0.f : a.ivar[row + j] * w2;
-    }
-    if (tid == 0) a.s.neff[spec] = (int)sOut[4];
+    for (int i = 0; i < kNPL; ++i)
+      if (valid >> i & 1u) dst[i * BLOCK].y = (masked >> i & 1u) ? 0.f : iv[i + 1] * w2;
+    if (tid == 0) a.s.neff[spec] = n_kept;
   }
-  if (a.masked_out && tid == 0) a.masked_out[spec] = (int)(nv - sOut[4]);
+  if (a.masked_out && tid == 0) a.masked_out[spec] = nv - n_kept;
 }
 
 }  // namespace
