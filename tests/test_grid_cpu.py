@@ -22,7 +22,7 @@ def rule(w):
         if not np.all((w > 0) & np.isfinite(w)):
             return False
         dl = np.log10(w[-1] / w[0]) / (w.size - 1)
-        return bool(dl > 0 and np.all(np.abs(np.log10(w[1:] / w[:-1]) - dl) <= 1e-6 * dl))
+        return bool(dl > 0 and not np.any(np.abs(np.log10(w[1:] / w[:-1]) - dl) > 1e-6 * dl))
 
 
 @pytest.mark.parametrize("n", [32, 33, 1550, 8000])
