@@ -26,8 +26,7 @@
 // in LDS once F' has been read for the last time.
 #include <type_traits>
 
-#include "lasp_continuum.h"
-#include "lasp_prepare.h"
+#include "lasp_internal.h"
 
 // Every fused multiply-add below is written out: the compiler then forms none
 // of its own, and the pass gives the same bits in each of its variants (a

@@ -1,7 +1,7 @@
 // Once-per-fit preparation of each spectrum: pixel weights, the flux weight
 // w of Eq. 6, the lane-major (o/w, W w^2) layout read by the fused pass, and
 // the initial Adam state.
-#include "lasp_prepare.h"
+#include "lasp_internal.h"
 
 namespace lasp {
 namespace {

@@ -203,6 +203,57 @@ bool fused_supported(int block, int nd);
 int set_error(int code, const char *msg);
 size_t fused_smem_bytes(const Geometry &g);
 
+// ---- Nodes of the continuum moments ---------------------------------------
+constexpr int kMid = kNPL / 2;  // a lane's middle pixel: local expansions are about j0 + kMid
+
+// A lane's 17 pixels span so little of the row that every polynomial the
+// moments need is, on them, its own interpolant at a few nodes.  For nodes
+// x_mid + h tau_c (tau_c the seven Chebyshev points of [-8, 8] pixels, h = 2 / P)
+//   sum_i y_i p(x_i) = sum_c Y_c p(x_mid + h tau_c),  Y_c = sum_i L_c(t_i) y_i
+// up to the interpolation error of p.  The nodes are three pairs +-tau_c and
+// the middle, so the Lagrange weights fold into sums and differences of the
+// pixels at +-t:
+//   Y_+-c = sum_t E_c(t) (y_t + y_-t) +- sum_t O_c(t) (y_t - y_-t).
+constexpr int kNodes = 7, kPairs = kNodes / 2;
+struct MomentNodes {
+  double tau[kPairs] = {};
+  float e[kPairs + 1][kMid + 1] = {}, o[kPairs][kMid + 1] = {};  // e[kPairs]: the middle
+};
+constexpr MomentNodes make_moment_nodes() {
+  // cos((2 c - 1) pi / 14), c = 1, 2, 3
+  constexpr double cosines[kPairs] = {0.974927912181823607, 0.781831482468029809,
+                                      0.433883739117558120};
+  MomentNodes n{};
+  for (int c = 0; c < kPairs; ++c) n.tau[c] = kMid * cosines[c];
+  for (int c = 0; c <= kPairs; ++c)
+    for (int t = 0; t <= kMid; ++t) {
+      const bool mid = c == kPairs;
+      const double tc = mid ? 0.0 : n.tau[c];
+      double v = 1.0;  // the factors of the other pairs
+      for (int d = 0; d < kPairs; ++d)
+        if (d != c) v *= (t * t - n.tau[d] * n.tau[d]) / (tc * tc - n.tau[d] * n.tau[d]);
+      n.e[c][t] = (float)(mid ? v : 0.5 * v * t * t / (tc * tc));
+      if (!mid) n.o[c][t] = (float)(0.5 * v * t / tc);
+    }
+  return n;
+}
+inline constexpr MomentNodes kMomentNodes = make_moment_nodes();
+
+// Whether the nodes hold the moments' polynomials (degree n = 2 (nd - 1)) to
+// 1e-7 of their largest value on any lane of a row of P pixels: the Chebyshev
+// interpolation error 2 (a / 2)^7 |p^(7)| / 7!, a = 16 / P, with the seventh
+// derivative of a degree-n polynomial bounded by one, prod_{k < 7} (n^2 - k^2)
+// / (2 k + 1) (Markov).  Degree 10: 1,872 pixels and more, 8: 1,176, 6: 632,
+// 4: 240; shorter rows sum over the pixels.  (Six nodes would serve 3,684
+// pixels and more at degree 10; the step's pass measured 0.290 ms with six,
+// 0.293 with seven and 0.321 with both in one kernel, 16,384 x 3,900.)
+inline bool moment_nodes_hold(int nd, int P) {
+  const double n = 2.0 * (nd - 1), a = 16.0 / (double)P;
+  double b = 2.0;
+  for (int k = 0; k < kNodes; ++k) b *= (n * n - (double)k * k) / (2.0 * k + 1.0) / (k + 1.0) * 0.5 * a;
+  return b <= 1e-7;
+}
+
 // -------------------------------------------------------------- device side
 #ifdef __HIPCC__
 
@@ -496,6 +547,294 @@ __device__ inline void block_sum_lds_f32(const float (&acc)[NV], float *scratch,
     out[t] = s;
   }
   __syncthreads();
+}
+
+// ---- Preparation of one spectrum by one workgroup, shared by k_prepare and
+//      the one-shot passes: pixel weights, n_eff and the flux weight w of
+//      Eq. 6 (a flux quantile, Section 3.3 "Setting spectral weighting
+//      factors") -----------------------------------------------------------
+
+// Order-preserving map of a float to an unsigned key.
+__device__ inline uint32_t fkey(float f) {
+  uint32_t b = __float_as_uint(f);
+  return (b & 0x80000000u) ? ~b : (b | 0x80000000u);
+}
+__device__ inline float funkey(uint32_t k) {
+  uint32_t b = (k & 0x80000000u) ? (k & 0x7fffffffu) : ~k;
+  return __uint_as_float(b);
+}
+
+// Key of a pixel left out of the selection (no finite flux maps to it).
+constexpr uint32_t kNoKey = 0xffffffffu;
+
+// Scratch of the preparation in LDS, 32-bit words: two sets of per-wave
+// partial results, used in turn, so that one barrier serves each sum.
+constexpr int kPrepScratch = 3 * 8;
+
+// What the preparation finds out about one spectrum.
+struct RowInfo {
+  int n_eff;
+  uint32_t any_bad;  // some obs or ivar is not finite
+  float w;
+};
+
+// Reads the spectrum's row, thread t pixels t + i BLOCK (coalesced), into
+// o and iv -- (0, 0) for a pixel without weight -- and finds its flux weight:
+// the requested quantile q of the valid fluxes (linear interpolation between
+// order statistics), rounded to the nearest power of two so that o/w and
+// W w^2 are exact in floating point.  The objective does not depend on w.
+//
+// Only the power of two is needed, so the order statistics are bracketed
+// instead of sorted out: counts of the valid fluxes below and up to the two
+// ends of one power's interval (2^(b - 1/2), 2^(b + 1/2)), drawn in by 2^-12
+// of their value, show that both order statistics next to the quantile, and
+// with them q, lie inside it; then w = 2^b whatever q is.  b starts from the
+// mean flux and moves by one towards the quantile, which takes one or two
+// counts over registers (four operations per pixel) on a spectrum.  Where
+// the bracket does not close -- order statistics on both sides of an end or
+// within 2^-12 of it, nonpositive or widely scattered fluxes -- q is formed
+// from the order statistics themselves, found bit by bit by the same kind of
+// counts over order-preserving keys.
+//
+// Every thread of the workgroup gets the same RowInfo.  scratch: kPrepScratch
+// words of LDS, free again after a barrier.
+template <int BLOCK>
+__device__ inline RowInfo prepare_row(const float *o_row, const float *i_row, int P, float quantile,
+                                      uint32_t *scratch, float (&o)[kNPL], float (&iv)[kNPL]) {
+  constexpr int NW = BLOCK / 64;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  int slot = 0;
+  auto total = [&](int v) {  // sum over the workgroup
+    uint32_t *red = scratch + 8 * slot;
+    slot ^= 1;
+    v = wave_sum(v);
+    if (lane == 0) red[wave] = (uint32_t)v;
+    __syncthreads();
+    int t = 0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) t += (int)red[w];
+    return __builtin_amdgcn_readfirstlane(t);
+  };
+#pragma unroll
+  for (int i = 0; i < kNPL; ++i) {
+    const int j = min(tid + i * BLOCK, P - 1);
+    o[i] = o_row[j];
+    iv[i] = i_row[j];
+  }
+  int n = 0;
+  float sum = 0.f, fin = 0.f;  // fin: NaN once a value is not finite
+#pragma unroll
+  for (int i = 0; i < kNPL; ++i) {
+    fin = fmaf(o[i], 0.f, fmaf(iv[i], 0.f, fin));
+    const bool ok = isfinite(o[i]) && isfinite(iv[i]) && iv[i] > 0.f && tid + i * BLOCK < P;
+    n += ok ? 1 : 0;
+    sum += ok ? o[i] : 0.f;
+    o[i] = ok ? o[i] : INFINITY;  // above every valid flux in the counts
+    iv[i] = ok ? iv[i] : 0.f;
+  }
+  RowInfo r{0, 0, 1.f};
+  sum = wave_sum(sum);
+  if (lane == 0) scratch[16 + wave] = __float_as_uint(sum);
+  n = total(n | (fin != fin ? 1 << 16 : 0));  // at most 8,704 pixels, 512 flags
+  r.n_eff = n & 0xffff;
+  r.any_bad = n >> 16 != 0 ? 1u : 0u;
+  sum = 0.f;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) sum += __uint_as_float(scratch[16 + w]);
+  auto clear = [&]() {
+#pragma unroll
+    for (int i = 0; i < kNPL; ++i) o[i] = iv[i] > 0.f ? o[i] : 0.f;
+  };
+  if (!(quantile > 0.f) || r.n_eff == 0) {
+    clear();
+    return r;
+  }
+
+  const float pos = quantile * (float)(r.n_eff - 1);
+  const uint32_t k0 = (uint32_t)floorf(pos);
+  const float frac = pos - (float)k0;
+  const uint32_t k1 = frac > 0.f && k0 + 1 < (uint32_t)r.n_eff ? k0 + 1 : k0;
+  float w = 1.f;
+  bool found = false;
+  {
+    const float mean = sum / (float)r.n_eff;
+    int b = 0, dir = 0;
+    bool go = mean > 0.f && isfinite(mean) && k0 < (uint32_t)r.n_eff;
+    if (go) b = __builtin_amdgcn_readfirstlane((int)rintf(log2f(mean)));
+    for (int it = 0; it < 8 && go; ++it) {
+      if (b < -100 || b > 100) break;
+      const float lo = ldexpf(0.70728f, b), hi = ldexpf(1.41387f, b);
+      int c_lo = 0, c_hi = 0;
+#pragma unroll
+      for (int i = 0; i < kNPL; ++i) {
+        c_lo += o[i] < lo ? 1 : 0;
+        c_hi += o[i] <= hi ? 1 : 0;
+      }
+      const uint32_t c = (uint32_t)total(c_lo | c_hi << 16);
+      if ((c & 0xffffu) <= k0 && k1 < c >> 16) {
+        w = exp2f((float)b);
+        found = true;
+        break;
+      }
+      const int step = k0 < (c & 0xffffu) ? -1 : 1;
+      go = dir == 0 || step == dir;  // past the quantile: the ends part it
+      dir = step;
+      b += step;
+    }
+  }
+  if (!found) {
+    // keys in place of the fluxes; the k0-th smallest is the largest value
+    // that at most k0 keys are below
+    uint32_t kth = 0;
+#pragma unroll
+    for (int i = 0; i < kNPL; ++i) o[i] = __uint_as_float(iv[i] > 0.f ? fkey(o[i]) : kNoKey);
+#pragma unroll 1
+    for (uint32_t bit = 0x80000000u; bit != 0; bit >>= 1) {
+      const uint32_t t = kth | bit;
+      int c = 0;
+#pragma unroll
+      for (int i = 0; i < kNPL; ++i) c += __float_as_uint(o[i]) < t ? 1 : 0;
+      if ((uint32_t)total(c) <= k0) kth = t;
+    }
+    const float v0 = funkey(kth);
+    float q = v0;
+    if (k1 > k0) {
+      // the next one: the same key if another pixel holds it, else the
+      // smallest above it
+      int c = 0;
+      uint32_t m = kNoKey;
+#pragma unroll
+      for (int i = 0; i < kNPL; ++i) {
+        const uint32_t key = __float_as_uint(o[i]);
+        c += key <= kth ? 1 : 0;
+        m = key > kth ? min(m, key) : m;
+      }
+#pragma unroll
+      for (int s = 32; s > 0; s >>= 1) m = min(m, (uint32_t)__shfl_xor(m, s));
+      if (lane == 0) scratch[16 + wave] = m;  // the mean's partials have been read
+      const uint32_t upto = (uint32_t)total(c);
+#pragma unroll
+      for (int v = 0; v < NW; ++v) m = min(m, scratch[16 + v]);
+      const float v1 = k1 < upto ? v0 : funkey(m);
+      q = v0 + frac * (v1 - v0);
+    }
+    if (q > 0.f && isfinite(q)) w = exp2f(rintf(log2f(q)));
+#pragma unroll
+    for (int i = 0; i < kNPL; ++i) o[i] = funkey(__float_as_uint(o[i]));
+  }
+  if (!(w > 0.f) || !isfinite(w) || !isfinite(1.f / (w * w))) w = 1.f;
+  r.w = w;
+  clear();
+  return r;
+}
+
+// ---- Continuum moments of one lane's pixels (Eq. 6).  Every fused
+//      multiply-add is written out and none left to the compiler, so that
+//      all kernels get the same bits -------------------------------------
+
+// Sums over one lane of y_j T_l (l <= D), y_j T_D T_k (k = 1..D) and z_j T_n
+// (n <= D), one abscissa at a time.
+template <int ND>
+struct MomentSums {
+  float nu[ND], q[ND], rr[ND];  // q[0] unused
+  __device__ inline void clear() {
+#pragma unroll
+    for (int k = 0; k < ND; ++k) nu[k] = q[k] = rr[k] = 0.f;
+  }
+  __device__ inline void add(float x, float y, float z) {
+#pragma clang fp contract(off)
+    const float x2 = x + x;
+    float t[ND];  // T_0(x) .. T_D(x)
+    t[0] = 1.f;
+    t[1] = x;
+#pragma unroll
+    for (int l = 2; l < ND; ++l) t[l] = fmaf(x2, t[l - 1], -t[l - 2]);
+    const float yd = y * t[ND - 1];
+    nu[0] += y;
+    rr[0] += z;
+#pragma unroll
+    for (int l = 1; l < ND; ++l) {
+      nu[l] = fmaf(y, t[l], nu[l]);
+      q[l] = fmaf(yd, t[l], q[l]);
+      rr[l] = fmaf(z, t[l], rr[l]);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  }
+};
+
+// The same sums by nodes: the pixels' W F''^2 and W F'' o are folded onto the
+// nodes, 24 operations per pair of pixels against 2 x 47 (D = 10), and only
+// the nodes go through the Chebyshev recurrence.
+template <int ND>
+__device__ inline void moments_by_nodes(MomentSums<ND> &s, float x_mid, float h,
+                                        const float (&fpp)[kNPL], const float2 (&ow)[kNPL]) {
+#pragma clang fp contract(off)
+  float ye[kPairs + 1], yo[kPairs], ze[kPairs + 1], zo[kPairs];
+  {
+    const float wf = ow[kMid].y * fpp[kMid];
+    const float y = wf * fpp[kMid], z = wf * ow[kMid].x;
+#pragma unroll
+    for (int c = 0; c <= kPairs; ++c) {
+      ye[c] = y * kMomentNodes.e[c][0];
+      ze[c] = z * kMomentNodes.e[c][0];
+    }
+#pragma unroll
+    for (int c = 0; c < kPairs; ++c) yo[c] = zo[c] = 0.f;
+  }
+#pragma unroll
+  for (int t = 1; t <= kMid; ++t) {
+    const float wp = ow[kMid + t].y * fpp[kMid + t], wm = ow[kMid - t].y * fpp[kMid - t];
+    const float yp = wp * fpp[kMid + t], ym = wm * fpp[kMid - t];
+    const float zp = wp * ow[kMid + t].x, zm = wm * ow[kMid - t].x;
+    const float ys = yp + ym, yd = yp - ym, zs = zp + zm, zd = zp - zm;
+#pragma unroll
+    for (int c = 0; c <= kPairs; ++c) {
+      ye[c] = fmaf(kMomentNodes.e[c][t], ys, ye[c]);
+      ze[c] = fmaf(kMomentNodes.e[c][t], zs, ze[c]);
+    }
+#pragma unroll
+    for (int c = 0; c < kPairs; ++c) {
+      yo[c] = fmaf(kMomentNodes.o[c][t], yd, yo[c]);
+      zo[c] = fmaf(kMomentNodes.o[c][t], zd, zo[c]);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  s.clear();
+#pragma unroll
+  for (int c = 0; c < kPairs; ++c) {
+    const float dx = (float)kMomentNodes.tau[c] * h;
+    s.add(x_mid + dx, ye[c] + yo[c], ze[c] + zo[c]);
+    s.add(x_mid - dx, ye[c] - yo[c], ze[c] - zo[c]);
+  }
+  s.add(x_mid, ye[kPairs], ze[kPairs]);
+}
+
+// One lane's moments nu_0..nu_D, q_1..q_D, r_0..r_D in acc, by the nodes or
+// over the pixels.  (Two kernels, not a branch: both forms in one kernel
+// spilled 68 B per lane at 128 registers, either alone none.)
+template <bool NODES, int ND>
+__device__ inline void lane_moments(int j0, int P, const float (&fpp)[kNPL],
+                                    const float2 (&ow)[kNPL], float (&acc)[3 * ND - 1]) {
+#pragma clang fp contract(off)
+  const float h = 2.f / (float)P;
+  MomentSums<ND> s;
+  if constexpr (NODES) {
+    moments_by_nodes<ND>(s, fmaf((float)(j0 + kMid), h, -1.f), h, fpp, ow);
+  } else {
+    const float x0 = fmaf((float)j0, h, -1.f);
+    s.clear();
+#pragma unroll
+    for (int i = 0; i < kNPL; ++i) {
+      const float wf = ow[i].y * fpp[i];
+      s.add(fmaf((float)i, h, x0), wf * fpp[i], wf * ow[i].x);
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < ND; ++k) acc[k] = s.nu[k];
+#pragma unroll
+  for (int k = 1; k < ND; ++k) acc[ND - 1 + k] = s.q[k];
+#pragma unroll
+  for (int k = 0; k < ND; ++k) acc[2 * ND - 1 + k] = s.rr[k];
 }
 
 #endif  // __HIPCC__
