@@ -126,14 +126,12 @@ extern "C" {
  *                  next step du^T q is below 1e-6, when an accepted step
  *                  lowers chi2 by less than 1e-10 relative or moves u by
  *                  less than 1e-7, or when lambda exceeds 1e10
- *                  (LASP_ST_POLISH_LIMIT if the iteration limit came first).  The paper proposes adding curvature
- *                  information to its Adam stage (Section 4.5); n_steps = 0
- *                  with polish_iters > 0 is a plain LM fit.  Every 4
- *                  iterations the number of spectra still iterating is
- *                  counted on the device; once a count reads 0 the call
- *                  stops enqueuing iterations (it waits on its stream for
- *                  the count of 4 iterations earlier), which changes no
- *                  result: a stopped spectrum's iterations do nothing.
+ *                  (LASP_ST_POLISH_LIMIT if the iteration limit came first).
+ *                  The paper proposes adding curvature information to its
+ *                  Adam stage (Section 4.5); n_steps = 0 with polish_iters
+ *                  > 0 is a plain LM fit.  Each spectrum iterates on its own
+ *                  until its own stop, in one launch, with the contraction
+ *                  in FP32 whatever the precision option.
  *  clean_every, clean_max  the Clean strategy of Section 2.2 (steps 6 and 8):
  *                  after every clean_every Adam steps (at most clean_max
  *                  times; the paper's 30 and 11) the model at the current

@@ -10,11 +10,22 @@
 // forward mode: dF''/du_t = G (x) dF'/du_t for t = 1..3 (dF'/du_t from the
 // derivative rows of the interpolator contraction) and
 // dF''/du_{4,5} = (dG/dmu, dG/dsigma) (x) F' times the chain factors.
-// Optionally the model Jacobian d(C F'')/du at fixed continuum is written,
-// and the Gauss-Newton normal equations of the profiled residual, S du = q
-// with q = Ju^T W e (no continuum term: Jb^T W e = 0 at the least-squares
-// continuum), for the Levenberg-Marquardt polish.
+// The kernel is an evaluation of its own: it also gives chi2, the model, the
+// status and the model Jacobian d(C F'')/du at fixed continuum, from the same
+// sums as the fused pass (chi2 and the status bit for bit).
+//
+// The Levenberg-Marquardt polish (the curvature step that the paper's Section
+// 4.5, future improvements, proposes for the Adam stage) is the same
+// evaluation in a loop.  S du = q with q = Ju^T W e (no continuum term:
+// Jb^T W e = 0 at the least-squares continuum) are the Gauss-Newton normal
+// equations of the residual with the continuum profiled out; a step solves
+// (S + lambda diag(S)) du = q in FP64, and is kept when chi2 falls (lambda /
+// 10) or dropped (lambda * 10), as in Marquardt's method.
 #include "lasp_internal.h"
+
+// Every fused multiply-add is written out, so that chi2 and the status are
+// those of the fused pass in each mode.
+#pragma clang fp contract(off)
 
 namespace lasp {
 namespace {
@@ -26,40 +37,183 @@ struct IntC {
   static constexpr int value = V;
 };
 
+// What a launch does: kOneShot prepares its spectra from obs and ivar itself;
+// kPrepared takes them from s.ow; kLm too, and iterates.
+constexpr int kOneShot = 0, kPrepared = 1, kLm = 2;
+
 struct CovLayout {
   int ks;
   int k_off;   // floats: taps [n_arms][3][ks]
-  int d_off;   // floats: columns dF''/du_{1..3} [3][kNPL * block], lane-major pixels
+  int d_off;   // floats: columns dF''/du_{1..3} [3][kNPL * block], pixel order
   int x_off;   // bytes: doubles
   int bytes;
 };
 
-// The staged F' row region (floats [0, k_off)) is reused as the reduction
-// scratch of block_sum_lds once every convolution is done.
+// The staged row region (floats [0, k_off)) holds F' rows for the
+// convolutions, then the reductions' scratch and rows on their way out.
 __host__ __device__ inline CovLayout cov_layout(const Geometry &g, int nwaves) {
   CovLayout L;
   int cols = kOffF + (g.ldF > kNPL * g.block ? g.ldF : kNPL * g.block) + 32;
-  if (cols < nwaves * 1024) cols = nwaves * 1024;
   L.ks = ((2 * g.M + 1 + 7) & ~7) + 8;
   L.k_off = (cols + 3) & ~3;
   L.d_off = (L.k_off + g.n_arms * 3 * L.ks + 3) & ~3;
   const int fl_end = L.d_off + 3 * kNPL * g.block;
   L.x_off = ((fl_end * 4) + 15) & ~15;
-  // doubles: reduction [nwaves][64], moments [64], JuJu + q + chi2 [32],
-  // X [16][8], work [64], scalars [16]
-  L.bytes = L.x_off + 8 * (nwaves * 64 + 64 + 32 + 128 + 64 + 16);
+  // doubles: reduction [nwaves][64], moments [64], JuJu + q [32], X [128],
+  // work [64], mirrored moments [64], power series [32], scalars [16], LM
+  // state [80]; then the feature rows [60][4] as floats
+  L.bytes = L.x_off + 8 * (nwaves * 64 + 64 + 32 + 128 + 64 + 64 + 32 + 16 + 80) + 4 * 4 * kNB * kMaxClasses;
   return L;
 }
 
-// Two waves per SIMD (two workgroups per CU, as the LDS allows) although the
-// registers then spill some values to scratch: the measured time per
-// launch falls by about a fifth against one wave per SIMD without spills.
-template <int BLOCK, int ND>
-__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(2))) void k_cov(Geometry g, State s, double blo0, double bhi0,
-                                               double blo1, double bhi1, double blo2, double bhi2,
-                                               double out_scale3, double out_scale4,
-                                               double *out_cov, float *out_jac,
-                                               double *out_normal, const int *active) {
+// 5x5 symmetric positive definite solve (Cholesky, FP64); false if not SPD.
+__device__ inline bool chol5(double (&a)[kNP][kNP], double (&x)[kNP]) {
+#pragma unroll
+  for (int j = 0; j < kNP; ++j) {
+    double d = a[j][j];
+#pragma unroll
+    for (int k = 0; k < j; ++k) d = fma(-a[j][k], a[j][k], d);
+    if (!(d > 0.0) || !isfinite(d)) return false;
+    const double l = sqrt(d);
+    a[j][j] = l;
+#pragma unroll
+    for (int i = j + 1; i < kNP; ++i) {
+      double v = a[i][j];
+#pragma unroll
+      for (int k = 0; k < j; ++k) v = fma(-a[i][k], a[j][k], v);
+      a[i][j] = v / l;
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < kNP; ++i) {
+    double v = x[i];
+#pragma unroll
+    for (int k = 0; k < i; ++k) v = fma(-a[i][k], x[k], v);
+    x[i] = v / a[i][i];
+  }
+#pragma unroll
+  for (int i = kNP - 1; i >= 0; --i) {
+    double v = x[i];
+#pragma unroll
+    for (int k = i + 1; k < kNP; ++k) v = fma(-a[k][i], x[k], v);
+    x[i] = v / a[i][i];
+  }
+  return true;
+}
+
+// State of one spectrum's Levenberg-Marquardt iteration, in LDS.
+struct LmState {
+  double S[kNP * kNP], q[kNP];  // normal equations at cur
+  double c0;                    // chi2 there (NaN: equations not positive definite)
+  double lambda, step_inf;      // damping, max |du| of the trial step (NaN: no step)
+  double nS[kNP * kNP];         // S at the evaluated point
+  float cur[8], pt[8];          // kept point, evaluated point
+  int done, limit;
+};
+static_assert(sizeof(LmState) <= 80 * sizeof(double), "LM state fits its LDS");
+
+// After the evaluation at pt (chi2 c1, normal equations nS and q1, positive
+// definite if ok): keep or drop the trial step, test for the end, and form the
+// next trial point.  One wave, all lanes alike; lane 0 writes.
+__device__ inline void lm_update(LmState &m, const double *q1, double c1, bool ok, int it,
+                                 int last, int lane) {
+  double c0 = m.c0, lam = m.lambda;
+  const double dinf = m.step_inf;
+  bool take, done = false;
+  if (it == 0) {
+    take = true;
+    lam = 1e-3;
+  } else if (isfinite(dinf) && isfinite(c1) && c1 < c0) {
+    take = true;
+    lam = fmax(lam * 0.1, 1e-15);
+    done = (c0 - c1) <= kLmDropTol * c0 || dinf <= kLmStepTol;
+  } else {
+    take = false;
+    lam *= 10.0;
+    done = lam > kLmLambdaMax || (isfinite(dinf) && dinf <= kLmStepTol) || !isfinite(c0);
+  }
+  double a[kNP][kNP], x[kNP], q[kNP];
+  float u[kNP];
+#pragma unroll
+  for (int i = 0; i < kNP; ++i) {
+    q[i] = take ? q1[i] : m.q[i];
+    x[i] = q[i];
+    u[i] = take ? m.pt[i] : m.cur[i];
+#pragma unroll
+    for (int j = 0; j < kNP; ++j) a[i][j] = take ? m.nS[i * kNP + j] : m.S[i * kNP + j];
+  }
+  if (take) c0 = ok ? c1 : NAN;
+  wave_lds_sync();  // every lane has read the old state
+  if (lane == 0) {
+#pragma unroll
+    for (int i = 0; i < kNP; ++i) {
+      m.q[i] = q[i];
+      m.cur[i] = u[i];
+#pragma unroll
+      for (int j = 0; j < kNP; ++j) m.S[i * kNP + j] = a[i][j];
+    }
+    m.c0 = c0;
+    m.lambda = lam;
+  }
+  int limit = 0;
+  double step = 0.0;
+  if (!done && it == last) {
+    limit = 1;
+    done = true;
+  }
+  if (!done) {
+    double dmax = 0.0;
+#pragma unroll
+    for (int t = 0; t < kNP; ++t) dmax = fmax(dmax, a[t][t]);
+#pragma unroll
+    for (int t = 0; t < kNP; ++t) a[t][t] = fma(lam, fmax(a[t][t], 1e-12 * dmax), a[t][t]);
+    if (chol5(a, x)) {
+      // predicted chi2 decrease of the Gauss-Newton model, du^T q: below the
+      // tolerance there is nothing left to gain and the spectrum stops here
+      double dec = 0.0;
+#pragma unroll
+      for (int t = 0; t < kNP; ++t) dec = fma(x[t], q[t], dec);
+      done = dec < kLmDecreaseTol;
+#pragma unroll
+      for (int t = 0; t < kNP; ++t) {
+        step = fmax(step, fabs(x[t]));
+        if (lane == 0) m.pt[t] = (float)((double)u[t] + x[t]);
+      }
+    } else {
+      step = NAN;  // no step: the next evaluation raises lambda
+#pragma unroll
+      for (int t = 0; t < kNP; ++t)
+        if (lane == 0) m.pt[t] = u[t];
+    }
+  }
+  if (lane == 0) {
+    m.step_inf = step;
+    m.done = done ? 1 : 0;
+    m.limit = limit;
+  }
+}
+
+// Two waves per SIMD (two workgroups per CU, as the LDS allows).
+//
+// Bound by VALU issue: six convolutions, the moments, 15 + 5 products and 5
+// columns against the Chebyshev polynomials per pixel.  The taps stop at the
+// window's end, the continuum sums run over the lane's seven nodes (the five
+// X columns fold 17 pixels onto them too), the continuum is a local expansion
+// and chi2 comes from the same pass, so that no fused pass goes before.
+// Measured at 16,384 x 3,900, covariance with its preparation and evaluation:
+// 1.20 ms, against 1.31 + 0.25 + 0.45 ms as three kernels at the start;
+// Jacobian of 509 x 7,800 px in three arms: 0.134 ms against 0.33.
+//
+// kLm runs a spectrum's whole iteration in its workgroup: the four F' rows at
+// the trial point are formed here from the basis (in L2) -- the matrix cores'
+// FP32 products are chains of fused multiply-adds over k in order, and the
+// chain below is the same one bit for bit -- and nothing is launched, counted
+// or waited for between iterations.  A plain fit, at the start with six
+// launches per iteration for all spectra: one of 1,550 px 446 -> 166 us (the
+// kernel 124), 16,384 x 3,900 21.9 -> 7.7 ms.
+template <int BLOCK, int ND, int MODE, bool NODES>
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(2))) void k_cov(
+    Geometry g, State s, CovArgs ca) {
   constexpr int NW = BLOCK / 64;
   constexpr int NNU = 2 * ND - 1;
   constexpr int NMOM = NNU + ND;
@@ -72,514 +226,598 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(2))) void
   float *sD = sF + L.d_off;
   double *sRed = reinterpret_cast<double *>(smem + L.x_off);
   double *sMom = sRed + NW * 64;
-  double *sJJ = sMom + 64;    // JuJu packed [15], q [5], chi2
+  double *sJJ = sMom + 64;    // JuJu packed [15], q [5]
   double *sX = sJJ + 32;      // [ND][5]
   double *sW = sX + 128;      // work
-  double *sScal = sW + 64;
-  float *sBf = reinterpret_cast<float *>(sScal);       // [16] (b as float)
-  int *sHa = reinterpret_cast<int *>(sScal + 8);        // [kMaxArms]
-  float *sCs = reinterpret_cast<float *>(sScal + 12);   // [kMaxArms] chain factor for sigma
+  double *sNu = sW + 64;      // mirrored moments
+  double *sBd = sNu + 64;     // continuum power series
+  double *sScal = sBd + 32;   // [0] continuum solved, [1] chi2
+  int *sHa = reinterpret_cast<int *>(sScal + 4);        // [kMaxArms]
+  float *sCs = reinterpret_cast<float *>(sScal + 8);    // [kMaxArms] chain factor for sigma
+  LmState &lm = *reinterpret_cast<LmState *>(sScal + 16);
+  float4 *sPhi = reinterpret_cast<float4 *>(sScal + 16 + 80);  // [nb]: phi and its derivatives
 
   const int spec = blockIdx.x;
-  if (active && !active[spec]) return;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int P = g.P, M = g.M;
-  const int j0 = tid * kNPL;
-  const bool has_pix = j0 < P;
   const bool multi = g.n_arms > 1;
-
-  for (int q = tid; q < 3 * NCOL; q += BLOCK) sD[q] = 0.f;
-
-  // ---- taps G, dG/dmu, dG/dsigma per arm ---------------------------------
-  const double u4 = (double)s.u[(size_t)spec * kNP + 3];
-  const double u5 = (double)s.u[(size_t)spec * kNP + 4];
-  const double rv = g.rv_lo + (u4 + 1.0) * g.rv_half;
-  const double sg = g.sg_lo + (u5 + 1.0) * g.sg_half;
-  const double mu = rv * g.inv_scale;
-  const float cmu = (float)(g.rv_half * g.inv_scale);
-  if (wave == 0) {
-    for (int a = 0; a < g.n_arms; ++a) {
-      const double seff = g.bare ? sg : sqrt(sg * sg + g.arm_sig2[a]);
-      double spx = seff * g.inv_scale;
-      const bool fl = !(spx >= (double)kSigmaFloorPx);
-      if (fl) spx = (double)kSigmaFloorPx;
-      double hf = ceil(fabs(mu) + 5.0 * spx);
-      if (!(hf <= (double)M)) hf = (double)M;
-      const int H = (int)hf, T = 2 * H + 1;
-      double gv[3], dv[3];
-      double part = 0.0;
-#pragma unroll
-      for (int k = 0; k < 3; ++k) {
-        const int idx = lane + 64 * k;
-        double v = 0.0, d = 0.0;
-        if (64 * k < T && idx < T) {
-          d = (double)(idx - H) - mu;
-          v = exp(-d * d / (2.0 * spx * spx));
-        }
-        gv[k] = v;
-        dv[k] = d;
-        part += v;
-      }
-      const double inv_sum = 1.0 / wave_sum(part);
-      double s1 = 0.0, s2 = 0.0;
-#pragma unroll
-      for (int k = 0; k < 3; ++k) {
-        gv[k] *= inv_sum;
-        s1 += gv[k] * dv[k];
-        s2 += gv[k] * dv[k] * dv[k];
-      }
-      s1 = wave_sum(s1);
-      s2 = wave_sum(s2);
-      const double sp = spx;
-#pragma unroll
-      for (int k = 0; k < 3; ++k) {
-        const int idx = lane + 64 * k;
-        if (idx < L.ks) {
-          const bool in = idx < T;
-          sK[(a * 3 + 0) * L.ks + idx] = in ? (float)gv[k] : 0.f;
-          sK[(a * 3 + 1) * L.ks + idx] = in ? (float)(gv[k] * (dv[k] - s1) / (sp * sp)) : 0.f;
-          sK[(a * 3 + 2) * L.ks + idx] =
-              in ? (float)(gv[k] * (dv[k] * dv[k] - s2) / (sp * sp * sp)) : 0.f;
-        }
-      }
-      if (lane == 0) {
-        sHa[a] = H;
-        sCs[a] = fl ? 0.f : (float)(g.sg_half * g.inv_scale * (g.bare ? 1.0 : sg / seff));
-      }
-    }
+  if (MODE == kLm && threadIdx.x < kNP) {
+    const float u = s.u[(size_t)spec * kNP + threadIdx.x];
+    lm.pt[threadIdx.x] = u;
+    lm.cur[threadIdx.x] = u;
   }
-
-  // ---- forward-mode columns: F'' and dF''/du_t, one staged row at a time.
-  //      Row 0 gives F'' and the mu, sigma columns (kept in registers); rows
-  //      1..3 give the u1..u3 columns (kept in LDS) -----------------------
-  float f[kNPL], d3[kNPL], d4[kNPL];
-#pragma unroll
-  for (int i = 0; i < kNPL; ++i) f[i] = d3[i] = d4[i] = 0.f;
-  const int wp0 = wave * 64 * kNPL;
-  const int wp1 = min(wp0 + 64 * kNPL, P) - 1;
-  int wa_lo = 0, wa_hi = 0;
-  for (int a = 1; a < g.n_arms; ++a) {
-    if (g.arm_start[a] <= wp0) wa_lo = a;
-    if (g.arm_start[a] <= wp1) wa_hi = a;
-  }
-  constexpr int kStage = (kNPL * BLOCK / 4 + BLOCK - 1) / BLOCK;
   const int n4 = g.ldF / 4;
-  for (int row = 0; row < 4; ++row) {
-    __syncthreads();
-    {
-      const float4 *src = reinterpret_cast<const float4 *>(s.fp + (size_t)spec * s.fp_stride +
-                                                           (size_t)row * g.ldF);
-      float4 fst[kStage];
-#pragma unroll
-      for (int k = 0; k < kStage; ++k) fst[k] = src[min(tid + k * BLOCK, n4 - 1)];
-#pragma unroll
-      for (int k = 0; k < kStage; ++k)
-        *reinterpret_cast<float4 *>(sF + kOffF + 4 * min(tid + k * BLOCK, n4 - 1)) = fst[k];
-      for (int q = tid; q < kOffF; q += BLOCK) sF[q] = 0.f;
-      for (int q = tid; q < 32; q += BLOCK) sF[kOffF + g.ldF + q] = 0.f;
+  float *fp = s.fp + (size_t)spec * s.fp_stride;
+
+  // at most ca.last + 1 evaluations (kLm), else one
+#pragma unroll 1
+  for (int it = 0;; ++it) {
+    // the thread's index is made anew in each evaluation: addresses and range
+    // tests formed from it would be kept in registers over all of them
+    int tid = threadIdx.x;
+    if (MODE == kLm) opaque(tid);
+    const int lane = tid & 63, wave = tid >> 6;
+    const int j0 = tid * kNPL;
+    const bool has_pix = j0 < P;
+    const int wp0 = wave * 64 * kNPL;
+    const int wp1 = min(wp0 + 64 * kNPL, P) - 1;
+    int wa_lo = 0, wa_hi = 0;
+    for (int a = 1; a < g.n_arms; ++a) {
+      if (g.arm_start[a] <= wp0) wa_lo = a;
+      if (g.arm_start[a] <= wp1) wa_hi = a;
     }
-    __syncthreads();
-    if (!has_pix) continue;
-    for (int a = wa_lo; a <= wa_hi; ++a) {
-      const int H = sHa[a], T = 2 * H + 1;
-      const int nk = row == 0 ? 3 : 1;
-      float acc[3][kNPL];
+    __syncthreads();  // the point is set; the last evaluation's LDS is free
+    const float *u = MODE == kLm ? lm.pt : s.u + (size_t)spec * kNP;
+
+    // ---- taps G, dG/dmu, dG/dsigma per arm -------------------------------
+    const double u4 = (double)u[3], u5 = (double)u[4];
+    const double rv = g.rv_lo + (u4 + 1.0) * g.rv_half;
+    const double sg = g.sg_lo + (u5 + 1.0) * g.sg_half;
+    const double mu = rv * g.inv_scale;
+    const float cmu = (float)(g.rv_half * g.inv_scale);
+    if (wave == 0) {
+      for (int a = 0; a < g.n_arms; ++a) {
+        const double seff = g.bare ? sg : sqrt(sg * sg + g.arm_sig2[a]);
+        double spx = seff * g.inv_scale;
+        const bool fl = !(spx >= (double)kSigmaFloorPx);
+        if (fl) spx = (double)kSigmaFloorPx;
+        double hf = ceil(fabs(mu) + 5.0 * spx);
+        if (!(hf <= (double)M)) hf = (double)M;
+        const int H = (int)hf, T = 2 * H + 1;
+        const double inv2s2 = 0.5 / (spx * spx);
+        double gv[3], dv[3];
+        double part = 0.0;
 #pragma unroll
-      for (int q = 0; q < 3; ++q)
+        for (int k = 0; k < 3; ++k) {
+          const int idx = lane + 64 * k;
+          double v = 0.0, d = 0.0;
+          if (64 * k < T && idx < T) {
+            d = (double)(idx - H) - mu;
+            v = exp(-d * d * inv2s2);
+          }
+          gv[k] = v;
+          dv[k] = d;
+          part += v;
+        }
+        const double inv_sum = 1.0 / wave_sum(part);
+        double s1 = 0.0, s2 = 0.0;
 #pragma unroll
-        for (int i = 0; i < kNPL; ++i) acc[q][i] = 0.f;
-      for (int mb = 0; mb < T; mb += kTB) {
-        const float *wsrc = sF + kOffF + j0 + M + H - mb - (kTB - 1);
-        float w[NWIN];
+        for (int k = 0; k < 3; ++k) {
+          gv[k] *= inv_sum;
+          s1 = fma(gv[k], dv[k], s1);
+          s2 = fma(gv[k] * dv[k], dv[k], s2);
+        }
+        s1 = wave_sum(s1);
+        s2 = wave_sum(s2);
+        const double r2 = 1.0 / (spx * spx), r3 = r2 / spx;
 #pragma unroll
-        for (int q = 0; q < NWIN; ++q) w[q] = wsrc[q];
+        for (int k = 0; k < 3; ++k) {
+          const int idx = lane + 64 * k;
+          if (idx < L.ks) {
+            const bool in = idx < T;
+            sK[(a * 3 + 0) * L.ks + idx] = in ? (float)gv[k] : 0.f;
+            sK[(a * 3 + 1) * L.ks + idx] = in ? (float)(gv[k] * (dv[k] - s1) * r2) : 0.f;
+            sK[(a * 3 + 2) * L.ks + idx] = in ? (float)(gv[k] * fma(dv[k], dv[k], -s2) * r3) : 0.f;
+          }
+        }
+        if (lane == 0) {
+          sHa[a] = H;
+          sCs[a] = fl ? 0.f : (float)(g.sg_half * g.inv_scale * (g.bare ? 1.0 : sg / seff));
+        }
+      }
+    }
+    if constexpr (MODE == kLm) {
+      // ---- F' and its derivative rows at the trial point ------------------
+      if (wave == NW - 1) {
+        float pr[kNB * kMaxClasses];
+        if (g.nb == kNB) {
+          feature_row(u, lane & 3, pr);
 #pragma unroll
-        for (int q = 0; q < 3; ++q) {
-          if (q < nk) {
-            const float *K = sK + (a * 3 + q) * L.ks;
+          for (int k = 0; k < kNB; ++k)
+            if (lane < 4) reinterpret_cast<float *>(sPhi)[4 * k + lane] = pr[k];
+        } else {
+          feature_row_classes(g, u, lane & 3, pr);
+#pragma unroll
+          for (int k = 0; k < kNB * kMaxClasses; ++k)
+            if (lane < 4) reinterpret_cast<float *>(sPhi)[4 * k + lane] = pr[k];
+        }
+      }
+      __syncthreads();
+      const float4 *b4 = reinterpret_cast<const float4 *>(s.basis);
+#pragma unroll 1
+      for (int q = tid; q < n4; q += BLOCK) {
+        float4 r0 = make_float4(0.f, 0.f, 0.f, 0.f), r1 = r0, r2 = r0, r3 = r0;
+        auto fold = [&](float4 &r, float p, const float4 &b) {
+          r.x = fmaf(b.x, p, r.x);
+          r.y = fmaf(b.y, p, r.y);
+          r.z = fmaf(b.z, p, r.z);
+          r.w = fmaf(b.w, p, r.w);
+        };
+        for (int k0 = 0; k0 < g.nb; k0 += kNB) {
+#pragma unroll 10
+          for (int k = 0; k < kNB; ++k) {
+            const float4 b = b4[(size_t)(k0 + k) * n4 + q], p = sPhi[k0 + k];
+            fold(r0, p.x, b);
+            fold(r1, p.y, b);
+            fold(r2, p.z, b);
+            fold(r3, p.w, b);
+          }
+        }
+        // row 0 goes straight to its place, the derivative rows are read back
+        // by the thread that wrote them
+        *reinterpret_cast<float4 *>(sF + kOffF + 4 * q) = r0;
+        reinterpret_cast<float4 *>(fp + g.ldF)[q] = r1;
+        reinterpret_cast<float4 *>(fp + 2 * g.ldF)[q] = r2;
+        reinterpret_cast<float4 *>(fp + 3 * g.ldF)[q] = r3;
+      }
+    }
+
+    // ---- forward-mode columns: F'' and dF''/du_t, one staged row at a time.
+    //      Row 0 gives F'' and the mu, sigma columns (kept in registers); rows
+    //      1..3 give the u1..u3 columns (kept in LDS) -------------------------
+    float f[kNPL], d3[kNPL], d4[kNPL];
+#pragma unroll
+    for (int i = 0; i < kNPL; ++i) f[i] = d3[i] = d4[i] = 0.f;
+    for (int r = 0; r < 4; ++r) {
+      if (MODE != kLm || r > 0) {
+        const float4 *src = reinterpret_cast<const float4 *>(fp + (size_t)r * g.ldF);
+        // five named values: an array here would go to memory
+        static_assert((kNPL * BLOCK / 4 + BLOCK - 1) / BLOCK == 5, "float4 of a row per thread");
+        const int q0 = min(tid, n4 - 1), q1 = min(tid + BLOCK, n4 - 1),
+                  q2 = min(tid + 2 * BLOCK, n4 - 1), q3 = min(tid + 3 * BLOCK, n4 - 1),
+                  q4 = min(tid + 4 * BLOCK, n4 - 1);
+        const float4 x0 = src[q0], x1 = src[q1], x2 = src[q2], x3 = src[q3], x4 = src[q4];
+        __syncthreads();  // the previous row has been read
+        // threads past the row store the last float4 again (the same value)
+        float4 *dst = reinterpret_cast<float4 *>(sF + kOffF);
+        dst[q0] = x0;
+        dst[q1] = x1;
+        dst[q2] = x2;
+        dst[q3] = x3;
+        dst[q4] = x4;
+      }
+      if (r == 0) {
+        for (int q = tid; q < kOffF; q += BLOCK) sF[q] = 0.f;
+        for (int q = tid; q < 32; q += BLOCK) sF[kOffF + g.ldF + q] = 0.f;
+      }
+      __syncthreads();
+      if (!has_pix && r > 0) {  // lanes past the row: columns that weigh nothing
+#pragma unroll
+        for (int i = 0; i < kNPL; ++i) sD[(r - 1) * NCOL + j0 + i] = 0.f;
+      }
+      for (int a = wa_lo; has_pix && a <= wa_hi; ++a) {
+        const int H = __builtin_amdgcn_readfirstlane(sHa[a]), T = 2 * H + 1;
+        const int lo = multi ? g.arm_start[a] : 0;
+        const int hi = multi ? g.arm_start[a + 1] : P;
+        const float *K = sK + a * 3 * L.ks;
+        auto convolve = [&](auto nk, float (&acc)[decltype(nk)::value][kNPL]) {
+          constexpr int NK = decltype(nk)::value;
+#pragma unroll
+          for (int q = 0; q < NK; ++q)
+#pragma unroll
+            for (int i = 0; i < kNPL; ++i) acc[q][i] = 0.f;
+          for (int mb = 0; mb < T; mb += kTB) {
+            const float *wsrc = sF + kOffF + j0 + M + H - mb - (kTB - 1);
+            float w[NWIN];
+#pragma unroll
+            for (int q = 0; q < NWIN; ++q) w[q] = wsrc[q];
 #pragma unroll
             for (int t = 0; t < kTB; ++t) {
-              const float gk = K[mb + t];
+              if (mb + t >= T) break;  // wave uniform
 #pragma unroll
-              for (int i = 0; i < kNPL; ++i) acc[q][i] = fmaf(gk, w[i - t + kTB - 1], acc[q][i]);
+              for (int q = 0; q < NK; ++q) {
+                const float gk = K[q * L.ks + mb + t];
+#pragma unroll
+                for (int i = 0; i < kNPL; ++i) acc[q][i] = fmaf(gk, w[i - t + kTB - 1], acc[q][i]);
+              }
             }
           }
+        };
+        if (r == 0) {
+          float acc[3][kNPL];
+          convolve(IntC<3>{}, acc);
+          const float cs = sCs[a];
+#pragma unroll
+          for (int i = 0; i < kNPL; ++i)
+            if (!multi || (j0 + i >= lo && j0 + i < hi)) {
+              f[i] = acc[0][i];
+              d3[i] = cmu * acc[1][i];
+              d4[i] = cs * acc[2][i];
+            }
+        } else {
+          float acc[1][kNPL];
+          convolve(IntC<1>{}, acc);
+          // pixels past the last arm's end weigh nothing; they take zero
+#pragma unroll
+          for (int i = 0; i < kNPL; ++i)
+            if (!multi || (j0 + i >= lo && j0 + i < hi) || j0 + i >= P)
+              sD[(r - 1) * NCOL + j0 + i] = j0 + i < P ? acc[0][i] : 0.f;
         }
       }
-      const int lo = multi ? g.arm_start[a] : 0;
-      const int hi = multi ? g.arm_start[a + 1] : 0x7fffffff;
-      const float cs = sCs[a];
+    }
+    __syncthreads();  // every read of the staged row is done: sF becomes scratch
+
+    // ---- data -----------------------------------------------------------------
+    float2 ow[kNPL];
+    [[maybe_unused]] RowInfo row{};
+    if constexpr (MODE == kOneShot) {
+      float o[kNPL], iv[kNPL];
+      row = prepare_row<BLOCK>(ca.os.obs + (size_t)spec * P, ca.os.ivar + (size_t)spec * P, P,
+                               ca.os.quantile, reinterpret_cast<uint32_t *>(sRed), o, iv);
+      const float inv_w = 1.f / row.w, w2 = row.w * row.w;
+#pragma unroll
+      for (int i = 0; i < kNPL; ++i) sF[tid + i * BLOCK] = o[i] * inv_w;
+      __syncthreads();
+#pragma unroll
+      for (int i = 0; i < kNPL; ++i) ow[i].x = sF[j0 + i];
+      __syncthreads();
+#pragma unroll
+      for (int i = 0; i < kNPL; ++i) sF[tid + i * BLOCK] = iv[i] * w2;
+      __syncthreads();
+#pragma unroll
+      for (int i = 0; i < kNPL; ++i) ow[i].y = sF[j0 + i];
+      __syncthreads();
+      if (tid == 0) {
+        s.neff[spec] = row.n_eff;
+        s.wscale[spec] = row.w;
+      }
+    } else {
+      const float2 *src = s.ow + (size_t)spec * kNPL * BLOCK + tid;  // lane-major, coalesced
+#pragma unroll
+      for (int i = 0; i < kNPL; ++i) ow[i] = src[i * BLOCK];
+    }
+
+    // ---- continuum least squares, as in the fused pass ---------------------
+    {
 #pragma unroll
       for (int i = 0; i < kNPL; ++i) {
-        if (j0 + i >= lo && j0 + i < hi) {
-          if (row == 0) {
-            f[i] = acc[0][i];
-            d3[i] = cmu * acc[1][i];
-            d4[i] = cs * acc[2][i];
-          } else {
-            sD[(row - 1) * NCOL + j0 + i] = acc[0][i];
+        opaque(f[i]);
+        opaque(ow[i]);
+      }
+      float acc[NMOM];
+      int jb = j0;
+      opaque(jb);  // the Chebyshev values formed here are not kept for the passes below
+      lane_moments<NODES, ND>(jb, P, f, ow, acc);
+      block_sum_lds_f32<NW, NMOM>(acc, sF, sRed, sMom, lane, wave);
+    }
+    if (wave == 0) {
+      const bool ok = solve_continuum<ND>(sMom, sNu, sBd, g, lane);
+      if (lane == 0) sScal[0] = ok ? 1.0 : 0.0;
+    }
+    __syncthreads();
+    bool ok = __builtin_amdgcn_readfirstlane((int)(sScal[0] != 0.0)) != 0;
+
+    // ---- one pass per pixel: continuum C, residual e, the residual Jacobian
+    //      columns ju_t = C dF''/du_t (scaled in place: registers for mu and
+    //      sigma, LDS for u1..u3), and Ju^T W Ju (15), q = Ju^T W e (5) and
+    //      chi2, each lane in FP32, lanes and waves in FP64 --------------------
+    const float wsc = MODE == kOneShot ? row.w : s.wscale[spec];
+    {
+      constexpr int NC = expansion_terms(BLOCK, ND);
+      float cf[NC];
+      int jb = j0;
+      opaque(jb);
+      expand_continuum<ND, NC>(sBd, jb, P, cf);
+      float acc[20];
+#pragma unroll
+      for (int k = 0; k < 20; ++k) acc[k] = 0.f;
+      float chi2_part = 0.f, cmin = INFINITY;
+#pragma unroll
+      for (int i = 0; i < kNPL; ++i) {
+        const float t = (float)(i - kMid);
+        float C = cf[NC - 1];
+#pragma unroll
+        for (int k = NC - 2; k >= 0; --k) C = fmaf(C, t, cf[k]);
+        const float e = fmaf(-C, f[i], ow[i].x);
+        const float we = ow[i].y * e;
+        chi2_part = fmaf(we, e, chi2_part);
+        if constexpr (MODE != kLm) {
+          cmin = fminf(cmin, jb + i < P ? C : INFINITY);
+          if (ca.model_out) sF[jb + i] = (C * f[i]) * wsc;
+        }
+        float dd[kNP];
+#pragma unroll
+        for (int t3 = 0; t3 < 3; ++t3) {
+          const float v = sD[t3 * NCOL + jb + i] * C;
+          sD[t3 * NCOL + jb + i] = v;
+          dd[t3] = v;
+        }
+        d3[i] *= C;
+        d4[i] *= C;
+        dd[3] = d3[i];
+        dd[4] = d4[i];
+        int k = 0;
+#pragma unroll
+        for (int p = 0; p < kNP; ++p) {
+          const float wd = ow[i].y * dd[p];
+#pragma unroll
+          for (int q = 0; q <= p; ++q) {
+            acc[k] = fmaf(wd, dd[q], acc[k]);
+            ++k;
           }
         }
+#pragma unroll
+        for (int p = 0; p < kNP; ++p) acc[15 + p] = fmaf(we, dd[p], acc[15 + p]);
+        __builtin_amdgcn_sched_barrier(0);
       }
-    }
-  }
-  // data (lane-major, coalesced)
-  float2 ow[kNPL];
-  {
-    const float2 *src = s.ow + (size_t)spec * kNPL * BLOCK + tid;
-#pragma unroll
-    for (int i = 0; i < kNPL; ++i) ow[i] = src[i * BLOCK];
-  }
-  __syncthreads();  // every read of the staged row is done: sF becomes scratch
-  double *scratch = reinterpret_cast<double *>(sF);
-
-  // ---- continuum least squares (as in the fused pass): nu_l = sum W F''^2
-  //      T_l (l <= 2D) and r_n = sum W F'' o T_n (n <= D) from T_0 .. T_D
-  //      only (nu_{D+k} = 2 q_k - nu_{D-k}, q_k = sum W F''^2 T_D T_k); each
-  //      lane sums its pixels in FP32, the sums across lanes and waves are
-  //      FP64 ------------------------------------------------------------------
-  {
-    constexpr int D = ND - 1;
-    const float two_over_p = 2.f / (float)P;
-    float nu[ND], q[ND], rr[ND];
-#pragma unroll
-    for (int k = 0; k < ND; ++k) nu[k] = q[k] = rr[k] = 0.f;
-#pragma unroll
-    for (int i = 0; i < kNPL; ++i) {
-      const float x = fmaf((float)(j0 + i), two_over_p, -1.f);
-      const float wf = ow[i].y * f[i];
-      const float y = wf * f[i];
-      const float z = wf * ow[i].x;
-      const float x2 = x + x;
-      float t[ND];
-      t[0] = 1.f;
-      t[1] = x;
-#pragma unroll
-      for (int l = 2; l < ND; ++l) t[l] = fmaf(x2, t[l - 1], -t[l - 2]);
-      const float yd = y * t[D];
-      nu[0] += y;
-      rr[0] += z;
-#pragma unroll
-      for (int l = 1; l < ND; ++l) {
-        nu[l] = fmaf(y, t[l], nu[l]);
-        q[l] = fmaf(yd, t[l], q[l]);
-        rr[l] = fmaf(z, t[l], rr[l]);
-      }
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    float acc[NMOM];  // nu_0..nu_D, q_1..q_D, r_0..r_D
-#pragma unroll
-    for (int k = 0; k < ND; ++k) acc[k] = nu[k];
-#pragma unroll
-    for (int k = 1; k < ND; ++k) acc[D + k] = q[k];
-#pragma unroll
-    for (int k = 0; k < ND; ++k) acc[NNU + k] = rr[k];
-    block_sum_lds_f32<NW, NMOM>(acc, reinterpret_cast<float *>(scratch), sRed, sW, lane, wave);
-    if (tid < NMOM) sMom[tid] = (tid > D && tid < NNU) ? fma(2.0, sW[tid], -sW[2 * D - tid]) : sW[tid];
-    __syncthreads();
-  }
-  if (wave == 0) {
-    double a[ND + 1];
-    const bool row = lane < ND;
-#pragma unroll
-    for (int n = 0; n < ND; ++n) {
-      const int dd = lane > n ? lane - n : n - lane;
-      a[n] = row ? 0.5 * (sMom[min(lane + n, NNU - 1)] + sMom[min(dd, NNU - 1)]) : 0.0;
-    }
-    a[ND] = row ? sMom[NNU + min(lane, ND - 1)] : 0.0;
-    bool ok = true;
-#pragma unroll
-    for (int k = 0; k < ND; ++k) {
-      double piv[ND + 1];
-#pragma unroll
-      for (int n = k; n <= ND; ++n) piv[n] = read_lane(a[n], k);
-      ok = ok && (piv[k] > 0.0) && isfinite(piv[k]);
-      const double rp = 1.0 / piv[k];
-      if (lane == k) {
-#pragma unroll
-        for (int n = k; n <= ND; ++n) a[n] *= rp;
-      } else {
-        const double fct = a[k] * rp;
-#pragma unroll
-        for (int n = k + 1; n <= ND; ++n) a[n] = fma(-fct, piv[n], a[n]);
-        a[k] = 0.0;
-      }
-    }
-    if (row) sBf[lane] = ok ? (float)a[ND] : 0.f;
-    if (lane == 0) sScal[15] = ok ? 1.0 : 0.0;
-  }
-  __syncthreads();
-
-  // ---- one pass per pixel: continuum C, residual e, the residual Jacobian
-  //      columns ju_t = C dF''/du_t (scaled in place: registers for mu and
-  //      sigma, LDS for u1..u3), and Ju^T W Ju (15), q = Ju^T W e (5) and
-  //      chi2 in FP64 ------------------------------------------------------
-  {
-    float c[ND];
-#pragma unroll
-    for (int k = 0; k < ND; ++k) c[k] = sBf[k];
-#pragma unroll
-    for (int i = 0; i < kNPL; ++i) {
-      opaque(f[i]);
-      opaque(ow[i]);
-    }
-    const float two_over_p = 2.f / (float)P;
-    float acc[20];  // Ju^T W Ju packed (15), q = Ju^T W e (5): FP32 per lane
-#pragma unroll
-    for (int k = 0; k < 20; ++k) acc[k] = 0.f;
-    double chi2 = 0.0;
-#pragma unroll
-    for (int i = 0; i < kNPL; ++i) {
-      const float x = fmaf((float)(j0 + i), two_over_p, -1.f);
-      float b1 = 0.f, b2 = 0.f;
-#pragma unroll
-      for (int k = ND - 1; k >= 1; --k) {
-        const float bk = fmaf(x + x, b1, c[k] - b2);
-        b2 = b1;
-        b1 = bk;
-      }
-      const float C = fmaf(x, b1, c[0] - b2);
-      const float e = ow[i].x - C * f[i];
-      float dd[kNP];
-#pragma unroll
-      for (int t = 0; t < 3; ++t) {
-        // j0 + i < kNPL * BLOCK for every thread; columns are zero where no
-        // pixel is
-        const float v = sD[t * NCOL + j0 + i] * C;
-        sD[t * NCOL + j0 + i] = v;
-        dd[t] = v;
-      }
-      d3[i] *= C;
-      d4[i] *= C;
-      dd[3] = d3[i];
-      dd[4] = d4[i];
-      const float w = ow[i].y;
-      const float we = w * e;
-      int k = 0;
-#pragma unroll
-      for (int p = 0; p < kNP; ++p) {
-        const float wd = w * dd[p];
-#pragma unroll
-        for (int q = 0; q <= p; ++q) {
-          acc[k] = fmaf(wd, dd[q], acc[k]);
-          ++k;
+      {
+        const double cs = wave_sum((double)chi2_part);
+        const float cm = wave_min(cmin);
+        if (lane == 0) {
+          sRed[wave * 64 + 0] = cs;
+          sRed[wave * 64 + 1] = (double)cm;
         }
       }
+      __syncthreads();
+      if (tid == 0) {
+        double cs = 0.0, cm = INFINITY;
 #pragma unroll
-      for (int p = 0; p < kNP; ++p) acc[15 + p] = fmaf(we, dd[p], acc[15 + p]);
-      chi2 = fma((double)ow[i].y * (double)e, (double)e, chi2);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    if (out_jac && has_pix) {
-      const float wsc = s.wscale[spec];
-#pragma unroll
-      for (int i = 0; i < kNPL; ++i)
-        if (j0 + i < P) {
-          float *o = out_jac + (size_t)spec * kNP * P + j0 + i;
-#pragma unroll
-          for (int t = 0; t < 3; ++t) o[(size_t)t * P] = sD[t * NCOL + j0 + i] * wsc;
-          o[(size_t)3 * P] = d3[i] * wsc;
-          o[(size_t)4 * P] = d4[i] * wsc;
+        for (int w = 0; w < NW; ++w) {
+          cs += sRed[w * 64 + 0];
+          cm = fmin(cm, sRed[w * 64 + 1]);
         }
-    }
-    if (out_cov == nullptr && out_normal == nullptr) return;
-    block_sum_lds_f32<NW, 20>(acc, reinterpret_cast<float *>(scratch), sRed, sJJ, lane, wave);
-    double c2[1] = {chi2};
-    block_sum_lds<NW, 1>(c2, scratch, sRed, sJJ + 20, lane, wave);
-  }
-  // X[n][t] = Jb^T W Ju = sum W F'' T_n ju_t (Chebyshev T_n), FP32 per lane
-  // and FP64 across lanes: one pass for the LDS columns u1..u3 and one for
-  // the register columns mu, sigma, T_0 .. T_D formed once per pixel and pass
-  // (a pass that picked a register column by a run-time index would make
-  // the compiler keep them in memory).
-  auto xpass = [&](auto ncol, int t0, auto column) {
-    constexpr int NCX = decltype(ncol)::value;
-    int jb = j0;
-    opaque(jb);
-#pragma unroll
-    for (int i = 0; i < kNPL; ++i) {
-      opaque(f[i]);
-      opaque(ow[i]);
-    }
-    float acc[NCX * ND];  // [column][n]
-#pragma unroll
-    for (int n = 0; n < NCX * ND; ++n) acc[n] = 0.f;
-    const float two_over_p = 2.f / (float)P;
-#pragma unroll
-    for (int i = 0; i < kNPL; ++i) {
-      const float x = fmaf((float)(jb + i), two_over_p, -1.f);
-      const float x2 = x + x;
-      const float wf = ow[i].y * f[i];
-      float v[NCX];
-#pragma unroll
-      for (int c = 0; c < NCX; ++c) {
-        v[c] = wf * column(c, i);
-        acc[c * ND] += v[c];
-        acc[c * ND + 1] = fmaf(v[c], x, acc[c * ND + 1]);
+        sScal[1] = cs;
+        if (MODE != kLm && ca.set_status) {
+          const int n_eff = MODE == kOneShot ? row.n_eff : s.neff[spec];
+          s.chi2[spec] = cs;
+          uint32_t st;
+          if constexpr (MODE == kOneShot) {
+            st = (row.any_bad ? kStNonfinite : 0u) | (n_eff <= kNP + g.nd ? kStNoData : 0u) |
+                 box_bit(u);
+            if (ca.os.J) ca.os.J[spec] = n_eff > 0 ? (float)(cs / (double)n_eff) : 0.f;
+          } else {
+            st = s.status[spec] & ~(kStSingular | kStContNonpos | kStSigmaFloor);
+          }
+          if (!ok) st |= kStSingular;
+          if (!(cm > 0.0)) st |= kStContNonpos;
+          for (int a = 0; a < g.n_arms; ++a) {
+            const double seff = g.bare ? sg : sqrt(sg * sg + g.arm_sig2[a]);
+            if (!(seff * g.inv_scale >= (double)kSigmaFloorPx)) st |= kStSigmaFloor;
+          }
+          s.status[spec] = st;
+        }
       }
-      float tm = 1.f, tc = x;
+      if constexpr (MODE != kLm) {
+        // rows leave in pixel order (the barrier above ends the pass)
+        if (ca.model_out) {
+          for (int j = tid; j < P; j += BLOCK) ca.model_out[(size_t)spec * P + j] = sF[j];
+        }
+        if (ca.out_jac) {
+          float *o = ca.out_jac + (size_t)spec * kNP * P;
+          for (int j = tid; j < P; j += BLOCK) {
 #pragma unroll
-      for (int n = 2; n < ND; ++n) {
-        const float tn = fmaf(x2, tc, -tm);
+            for (int t = 0; t < 3; ++t) o[(size_t)t * P + j] = sD[t * NCOL + j] * wsc;
+          }
 #pragma unroll
-        for (int c = 0; c < NCX; ++c) acc[c * ND + n] = fmaf(v[c], tn, acc[c * ND + n]);
-        tm = tc;
-        tc = tn;
-      }
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    block_sum_lds_f32<NW, NCX * ND>(acc, reinterpret_cast<float *>(scratch), sRed, sW, lane, wave);
-    if (tid < NCX * ND) sX[(tid % ND) * kNP + t0 + tid / ND] = sW[tid];
-    __syncthreads();
-  };
-  xpass(IntC<3>{}, 0, [&](int c, int i) { return sD[c * NCOL + j0 + i]; });
-  xpass(IntC<2>{}, 3, [&](int c, int i) { return c == 0 ? d3[i] : d4[i]; });
-
-  // ---- wave 0: Y = A^{-1} X, S = JuJu - X^T Y, Sigma_u = s^2 S^{-1} --------
-  if (wave == 0) {
-    constexpr int NC = ND + kNP;
-    double a[NC];
-    const bool row = lane < ND;
+          for (int t = 3; t < kNP; ++t) {
+            __syncthreads();
 #pragma unroll
-    for (int n = 0; n < ND; ++n) {
-      const int dd = lane > n ? lane - n : n - lane;
-      a[n] = row ? 0.5 * (sMom[min(lane + n, NNU - 1)] + sMom[min(dd, NNU - 1)]) : 0.0;
-    }
-#pragma unroll
-    for (int t = 0; t < kNP; ++t) a[ND + t] = row ? sX[min(lane, ND - 1) * kNP + t] : 0.0;
-    bool ok = sScal[15] != 0.0;
-#pragma unroll
-    for (int k = 0; k < ND; ++k) {
-      double piv[NC];
-#pragma unroll
-      for (int n = k; n < NC; ++n) piv[n] = read_lane(a[n], k);
-      ok = ok && (piv[k] > 0.0) && isfinite(piv[k]);
-      const double rp = 1.0 / piv[k];
-      if (lane == k) {
-#pragma unroll
-        for (int n = k; n < NC; ++n) a[n] *= rp;
+            for (int i = 0; i < kNPL; ++i) sF[j0 + i] = (t == 3 ? d3[i] : d4[i]) * wsc;
+            __syncthreads();
+            for (int j = tid; j < P; j += BLOCK) o[(size_t)t * P + j] = sF[j];
+          }
+        }
+        if (!ca.out_cov) return;
+        __syncthreads();  // sF becomes scratch again; the chi2 parts are read
       } else {
-        const double fct = a[k] * rp;
-#pragma unroll
-        for (int n = k + 1; n < NC; ++n) a[n] = fma(-fct, piv[n], a[n]);
-        a[k] = 0.0;
+        __syncthreads();
       }
+      block_sum_lds_f32<NW, 20>(acc, sF, sRed, sJJ, lane, wave);
     }
-    if (row) {
+    // X[n][t] = Jb^T W Ju = sum W F'' T_n ju_t (Chebyshev T_n), FP32 per lane
+    // and FP64 across lanes: one pass for the LDS columns u1..u3 and one for
+    // the register columns mu, sigma (a pass that picked a register column by
+    // a run-time index would make the compiler keep them in memory).
+    {
 #pragma unroll
-      for (int t = 0; t < kNP; ++t) sW[lane * kNP + t] = a[ND + t];  // Y[n][t]
-    }
-    if (lane == 0) sScal[14] = ok ? 1.0 : 0.0;
-  }
-  __syncthreads();
-  if (wave == 0) {
-    bool ok = sScal[14] != 0.0;
-    // lanes 0..4 own rows of S, then invert S by Gauss-Jordan on [S | I]
-    double sr[2 * kNP];
-    const int r = lane < kNP ? lane : 0;
+      for (int i = 0; i < kNPL; ++i) f[i] = ow[i].y * f[i];
+      const float h = 2.f / (float)P;
+      auto xpass = [&](auto ncol, int t0, auto column) {
+        constexpr int NCX = decltype(ncol)::value;
+        int jb = j0;
+        opaque(jb);
+        float acc[NCX * ND];  // [column][n]
 #pragma unroll
-    for (int q = 0; q < kNP; ++q) {
-      const int p = r > q ? r : q, qq = r > q ? q : r;
-      double v = sJJ[p * (p + 1) / 2 + qq];
+        for (int n = 0; n < NCX * ND; ++n) acc[n] = 0.f;
+        auto add = [&](float x, const float (&v)[NCX]) {
+          const float x2 = x + x;
 #pragma unroll
-      for (int n = 0; n < ND; ++n) v -= sX[n * kNP + r] * sW[n * kNP + q];
-      sr[q] = v;
-      sr[kNP + q] = (r == q) ? 1.0 : 0.0;
-    }
-    if (out_normal && lane < kNP) {
-      // Gauss-Newton normal equations of the residual with the continuum
-      // profiled out: S du = q (rows of S, then q, then chi2)
-      double *o = out_normal + (size_t)spec * kNormalStride;
+          for (int c = 0; c < NCX; ++c) {
+            acc[c * ND] += v[c];
+            acc[c * ND + 1] = fmaf(v[c], x, acc[c * ND + 1]);
+          }
+          float tm = 1.f, tc = x;
 #pragma unroll
-      for (int q = 0; q < kNP; ++q) o[lane * kNP + q] = sr[q];
-      o[25 + lane] = sJJ[15 + lane];
-      if (lane == 0) o[30] = ok ? sJJ[20] : NAN;
-    }
-    if (out_cov) {
+          for (int n = 2; n < ND; ++n) {
+            const float tn = fmaf(x2, tc, -tm);
 #pragma unroll
-      for (int k = 0; k < kNP; ++k) {
-        double piv[2 * kNP];
+            for (int c = 0; c < NCX; ++c) acc[c * ND + n] = fmaf(v[c], tn, acc[c * ND + n]);
+            tm = tc;
+            tc = tn;
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        };
+        if constexpr (NODES) {
+          float Y[NCX][kNodes];
 #pragma unroll
-        for (int n = 0; n < 2 * kNP; ++n) piv[n] = read_lane(sr[n], k);
-        ok = ok && (piv[k] > 0.0) && isfinite(piv[k]);
-        const double rp = 1.0 / piv[k];
-        if (lane == k) {
+          for (int c = 0; c < NCX; ++c) {
+            fold_nodes([&](int i) { return f[i] * column(jb, c, i); }, Y[c]);
+            __builtin_amdgcn_sched_barrier(0);
+          }
+          const float x_mid = fmaf((float)(jb + kMid), h, -1.f);
 #pragma unroll
-          for (int n = 0; n < 2 * kNP; ++n) sr[n] *= rp;
+          for (int q = 0; q < kNodes; ++q) {
+            float v[NCX];
+#pragma unroll
+            for (int c = 0; c < NCX; ++c) v[c] = Y[c][q];
+            const float dx = q < 2 * kPairs ? (float)kMomentNodes.tau[q / 2 % kPairs] * h : 0.f;
+            add(q % 2 == 0 && q < 2 * kPairs ? x_mid + dx : x_mid - dx, v);
+          }
         } else {
-          const double fct = sr[k] * rp;
 #pragma unroll
-          for (int n = 0; n < 2 * kNP; ++n) sr[n] = fma(-fct, piv[n], sr[n]);
+          for (int i = 0; i < kNPL; ++i) {
+            float v[NCX];
+#pragma unroll
+            for (int c = 0; c < NCX; ++c) v[c] = f[i] * column(jb, c, i);
+            add(fmaf((float)(jb + i), h, -1.f), v);
+          }
         }
-      }
-      const int n_eff = s.neff[spec];
-      const double chi2 = sJJ[20];
-      const double s2 = n_eff > kNP ? chi2 / (double)(n_eff - kNP) : NAN;
-      if (lane < kNP) {
-        // physical units: Teff via dTeff = Teff ln10 dlog10Teff, the others by
-        // the box half-widths
-        const double lt = blo0 + 0.5 * ((double)s.u[(size_t)spec * kNP] + 1.0) * (bhi0 - blo0);
-        double jd[kNP];
-        jd[0] = 0.5 * (bhi0 - blo0) * exp10(lt) * kLn10;
-        jd[1] = 0.5 * (bhi1 - blo1);
-        jd[2] = 0.5 * (bhi2 - blo2);
-        jd[3] = out_scale3;
-        jd[4] = out_scale4;
-        double jr = jd[0];
-#pragma unroll
-        for (int q = 1; q < kNP; ++q)
-          if (q == lane) jr = jd[q];
-#pragma unroll
-        for (int q = 0; q < kNP; ++q) {
-          const double v = ok ? s2 * sr[kNP + q] * jr * jd[q] : NAN;
-          out_cov[((size_t)spec * kNP + lane) * kNP + q] = v;
-        }
-      }
-      if (lane == 0 && !ok) s.status[spec] |= kStSingular;
+        block_sum_lds_f32<NW, NCX * ND>(acc, sF, sRed, sW, lane, wave);
+        if (tid < NCX * ND) sX[(tid % ND) * kNP + t0 + tid / ND] = sW[tid];
+        __syncthreads();
+      };
+      xpass(IntC<3>{}, 0, [&](int jb, int c, int i) { return sD[c * NCOL + jb + i]; });
+      xpass(IntC<2>{}, 3, [&](int, int c, int i) { return c == 0 ? d3[i] : d4[i]; });
     }
+
+    // ---- wave 0: Y = A^{-1} X, S = JuJu - X^T Y --------------------------------
+    if (wave == 0) {
+      {
+        double a[ND + kNP], y[kNP], dg;
+        const double *nr = sNu + min(lane, ND - 1);
+#pragma unroll
+        for (int n = 0; n < ND; ++n) a[n] = 0.5 * (nr[ND - 1 + n] + nr[ND - 1 - n]);
+#pragma unroll
+        for (int t = 0; t < kNP; ++t) a[ND + t] = sX[min(lane, ND - 1) * kNP + t];
+        ok = eliminate<ND, ND + kNP>(a, lane, y, dg) && ok;
+        const double rd = 1.0 / dg;
+        if (lane < ND) {
+#pragma unroll
+          for (int t = 0; t < kNP; ++t) sW[lane * kNP + t] = y[t] * rd;  // Y[n][t]
+        }
+      }
+      wave_lds_sync();
+      // lanes 0..4 own rows of S
+      double sr[2 * kNP];
+      const int r = lane < kNP ? lane : 0;
+#pragma unroll
+      for (int q = 0; q < kNP; ++q) {
+        const int p = r > q ? r : q, qq = r > q ? q : r;
+        sr[q] = sJJ[p * (p + 1) / 2 + qq];
+        sr[kNP + q] = (r == q) ? 1.0 : 0.0;
+      }
+#pragma unroll
+      for (int n = 0; n < ND; ++n) {
+        const double x = sX[n * kNP + r];
+#pragma unroll
+        for (int q = 0; q < kNP; ++q) sr[q] = fma(-x, sW[n * kNP + q], sr[q]);
+      }
+      if constexpr (MODE == kLm) {
+        if (lane < kNP) {
+#pragma unroll
+          for (int q = 0; q < kNP; ++q) lm.nS[lane * kNP + q] = sr[q];
+        }
+        wave_lds_sync();
+        lm_update(lm, sJJ + 15, sScal[1], ok, it, ca.last, lane);
+      } else {
+        // Sigma_u = s^2 S^{-1} by Gauss-Jordan on [S | I]
+        double inv[kNP], dg;
+        ok = eliminate<kNP, 2 * kNP>(sr, lane, inv, dg) && ok;
+        const double rd = 1.0 / dg;
+        const int n_eff = MODE == kOneShot ? row.n_eff : s.neff[spec];
+        const double chi2 = sScal[1];
+        const double s2 = n_eff > kNP ? chi2 / (double)(n_eff - kNP) : NAN;
+        if (lane < kNP) {
+          // physical units: Teff via dTeff = Teff ln10 dlog10Teff, the others by
+          // the box half-widths
+          const double lt = ca.lo[0] + 0.5 * ((double)u[0] + 1.0) * (ca.hi[0] - ca.lo[0]);
+          double jd[kNP];
+#pragma unroll
+          for (int q = 0; q < kNP; ++q) jd[q] = 0.5 * (ca.hi[q] - ca.lo[q]);
+          jd[0] *= exp10(lt) * kLn10;
+          double jr = jd[0];
+#pragma unroll
+          for (int q = 1; q < kNP; ++q)
+            if (q == lane) jr = jd[q];
+#pragma unroll
+          for (int q = 0; q < kNP; ++q) {
+            const double v = ok ? s2 * (inv[q] * rd) * jr * jd[q] : NAN;
+            ca.out_cov[((size_t)spec * kNP + lane) * kNP + q] = v;
+          }
+        }
+        if (lane == 0 && !ok) s.status[spec] |= kStSingular;
+      }
+    }
+    if constexpr (MODE != kLm) return;
+    __syncthreads();
+    if (lm.done) break;  // at the latest after evaluation ca.last
   }
+  if (threadIdx.x < kNP) s.u[(size_t)spec * kNP + threadIdx.x] = lm.cur[threadIdx.x];
+  if (threadIdx.x == 0 && lm.limit) s.status[spec] |= kStPolishLimit;
 }
 
-template <int BLOCK, int ND>
-hipError_t launch_cov_t(const Geometry &g, const State &s, const double *lo, const double *hi,
-                        double *out_cov, float *out_jac, double *out_normal, const int *active,
-                        hipStream_t st) {
+template <int BLOCK, int ND, int MODE, bool NODES>
+hipError_t launch_cov_k(const Geometry &g, const State &s, const CovArgs &ca, hipStream_t st) {
   const CovLayout L = cov_layout(g, BLOCK / 64);
-  auto k = k_cov<BLOCK, ND>;
+  auto k = k_cov<BLOCK, ND, MODE, NODES>;
   hipError_t e =
       hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize, L.bytes);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k, dim3(g.B), dim3(BLOCK), L.bytes, st, g, s, lo[0], hi[0], lo[1], hi[1],
-                     lo[2], hi[2], 0.5 * (hi[3] - lo[3]), 0.5 * (hi[4] - lo[4]), out_cov, out_jac,
-                     out_normal, active);
+  hipLaunchKernelGGL(k, dim3(g.B), dim3(BLOCK), L.bytes, st, g, s, ca);
   return hipGetLastError();
 }
 
-template <int BLOCK>
-hipError_t launch_cov_b(const Geometry &g, const State &s, const double *lo, const double *hi,
-                        double *out_cov, float *out_jac, double *out_normal, const int *active,
-                        hipStream_t st) {
+template <int BLOCK, int ND, int MODE>
+hipError_t launch_cov_n(const Geometry &g, const State &s, const CovArgs &ca, hipStream_t st) {
+  if constexpr (BLOCK == 128) {
+    if (!moment_nodes_hold(ND, g.P)) return launch_cov_k<BLOCK, ND, MODE, false>(g, s, ca, st);
+  }
+  return launch_cov_k<BLOCK, ND, MODE, true>(g, s, ca, st);
+}
+
+template <int BLOCK, int MODE>
+hipError_t launch_cov_b(const Geometry &g, const State &s, const CovArgs &ca, hipStream_t st) {
   switch (g.nd) {
-    case 5: return launch_cov_t<BLOCK, 5>(g, s, lo, hi, out_cov, out_jac, out_normal, active, st);
-    case 7: return launch_cov_t<BLOCK, 7>(g, s, lo, hi, out_cov, out_jac, out_normal, active, st);
-    case 9: return launch_cov_t<BLOCK, 9>(g, s, lo, hi, out_cov, out_jac, out_normal, active, st);
-    case 11:
-      return launch_cov_t<BLOCK, 11>(g, s, lo, hi, out_cov, out_jac, out_normal, active, st);
+    case 5: return launch_cov_n<BLOCK, 5, MODE>(g, s, ca, st);
+    case 7: return launch_cov_n<BLOCK, 7, MODE>(g, s, ca, st);
+    case 9: return launch_cov_n<BLOCK, 9, MODE>(g, s, ca, st);
+    case 11: return launch_cov_n<BLOCK, 11, MODE>(g, s, ca, st);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+template <int MODE>
+hipError_t launch_cov_m(const Geometry &g, const State &s, const CovArgs &ca, hipStream_t st) {
+  switch (g.block) {
+    case 128: return launch_cov_b<128, MODE>(g, s, ca, st);
+    case 256: return launch_cov_b<256, MODE>(g, s, ca, st);
+    case 512: return launch_cov_b<512, MODE>(g, s, ca, st);
     default: return hipErrorInvalidValue;
   }
 }
 
 }  // namespace
 
-hipError_t launch_cov(const Geometry &g, const State &s, const double *lo, const double *hi,
-                      double *out_cov, float *out_jac, double *out_normal, const int *active,
-                      hipStream_t st) {
-  switch (g.block) {
-    case 128: return launch_cov_b<128>(g, s, lo, hi, out_cov, out_jac, out_normal, active, st);
-    case 256: return launch_cov_b<256>(g, s, lo, hi, out_cov, out_jac, out_normal, active, st);
-    case 512: return launch_cov_b<512>(g, s, lo, hi, out_cov, out_jac, out_normal, active, st);
-    default: return hipErrorInvalidValue;
-  }
+hipError_t launch_cov_oneshot(const Geometry &g, const State &s, const CovArgs &ca,
+                              hipStream_t st) {
+  return launch_cov_m<kOneShot>(g, s, ca, st);
+}
+
+hipError_t launch_cov(const Geometry &g, const State &s, const CovArgs &ca, hipStream_t st) {
+  return launch_cov_m<kPrepared>(g, s, ca, st);
+}
+
+hipError_t launch_lm(const Geometry &g, const State &s, const CovArgs &ca, hipStream_t st) {
+  return launch_cov_m<kLm>(g, s, ca, st);
 }
 
 }  // namespace lasp

@@ -38,20 +38,6 @@ namespace {
 
 constexpr int kOffF = 16;  // F' column c lives at sF[kOffF + c]
 
-// [x^n] T_k(x) for k, n <= 10, from T_k = 2x T_{k-1} - T_{k-2}.
-struct ChebPow {
-  int c[11][11];
-};
-constexpr ChebPow make_cheb_pow() {
-  ChebPow t{};
-  t.c[0][0] = 1;
-  t.c[1][1] = 1;
-  for (int k = 2; k < 11; ++k)
-    for (int n = 0; n <= k; ++n) t.c[k][n] = (n > 0 ? 2 * t.c[k - 1][n - 1] : 0) - t.c[k - 2][n];
-  return t;
-}
-constexpr ChebPow kChebPow = make_cheb_pow();
-
 // LDS of one workgroup.  Row region A holds, in turn, F' (column c at
 // kOffF + c) until the lag correlation has read it, then the g-bar row
 // (pixel j at 2M + j, j in [-2M, P + 2M + 32), zero outside [0, P)) for the
@@ -333,73 +319,8 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(4))) void
   //      holds nu_0..nu_D, then q_1..q_D with nu_{D+k} = 2 q_k - nu_{D-k}.
   if (wave == 0) {
     __builtin_amdgcn_s_setprio(3);
-    constexpr int D = ND - 1;
-    // nu_0 .. nu_2D mirrored about index D (sNu[D + l] = sNu[D - l] = nu_l),
-    // so row i reads nu_{i+n} and nu_{|i-n|} at fixed offsets from sNu + i
-    double *sNu = sRed;  // [3 D + 1], free until the residual's chi2 sums
-    {
-      const int l = min(lane, NNU - 1);
-      const double lo = sMom[l], hi = sMom[l <= D ? l : 2 * D - l];
-      const double nu = l <= D ? lo : fma(2.0, lo, -hi);
-      if (lane < NNU) sNu[D + lane] = nu;
-      if (lane >= 1 && lane <= D) sNu[D - lane] = nu;
-    }
-    // lanes past row D repeat row D; only rows 0..D are read or stored
-    const bool own = lane < ND;
-    double a[ND + 1];
-    a[ND] = sMom[NNU + min(lane, ND - 1)];
-    wave_lds_sync();
-    {
-      const double *nr = sNu + min(lane, ND - 1);
-#pragma unroll
-      for (int n = 0; n < ND; ++n) a[n] = 0.5 * (nr[D + n] + nr[D - n]);
-    }
-    // Gauss-Jordan without scaling the pivot rows: row k stays as it is and
-    // every other row loses its column-k entry; b_i = a_i[ND] / a_i[i] at
-    // the end.  The pivots are those of the scaled form.
-    bool ok = true;
-#pragma unroll
-    for (int k = 0; k < ND; ++k) {
-      double piv[ND + 1];
-#pragma unroll
-      for (int n = k; n <= ND; ++n) piv[n] = read_lane(a[n], k);
-      ok = ok && (piv[k] > 0.0) && isfinite(piv[k]);
-      // 1 / pivot: the hardware estimate and two Newton steps
-      double rp = __builtin_amdgcn_rcp(piv[k]);
-      rp = fma(rp, fma(-piv[k], rp, 1.0), rp);
-      rp = fma(rp, fma(-piv[k], rp, 1.0), rp);
-      const double f = lane == k ? 0.0 : a[k] * rp;
-#pragma unroll
-      for (int n = k + 1; n <= ND; ++n) a[n] = fma(-f, piv[n], a[n]);
-    }
-    {
-      double dg = a[0];
-#pragma unroll
-      for (int n = 1; n < ND; ++n) dg = lane == n ? a[n] : dg;
-      a[ND] = a[ND] / dg;
-    }
-    // The continuum as a power series in the pixel offset v = j - P/2 from
-    // the row's centre: x_j = h v with h = 2 / P, so C = sum_n m_n h^n v^n
-    // with m_n = sum_k b_k [x^n] T_k.  b goes through LDS to every lane of
-    // the wave, the coefficients m_n h^n back to LDS; each lane re-centres
-    // the series on its own pixels below.
-    if (own) sBd[16 + lane] = ok ? a[ND] : 0.0;
-    wave_lds_sync();
-    double bk[ND];
-#pragma unroll
-    for (int k = 0; k < ND; ++k) bk[k] = sBd[16 + k];
-    double mm[ND];
-#pragma unroll
-    for (int n = 0; n < ND; ++n) {
-      double m = 0.0;
-#pragma unroll
-      for (int k = n; k < ND; k += 2) m = fma(bk[k], (double)kChebPow.c[k][n], m);
-      mm[n] = m * g.hpow[n];
-    }
-    if (lane == 0) {
-#pragma unroll
-      for (int n = 0; n < ND; ++n) sBd[n] = mm[n];
-    }
+    // sRed is free until the residual's chi2 sums
+    const bool ok = solve_continuum<ND>(sMom, sRed, sBd, g, lane);
     if (lane == 0) sScal[0] = ok ? 1.0 : 0.0;
     __builtin_amdgcn_s_setprio(0);
   }
@@ -414,26 +335,9 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(4))) void
   float chi2_part = 0.f;  // this lane's 17 terms; lanes and waves add in FP64
   float cmin = INFINITY;
   {
-    // Taylor coefficients of t -> C(x_{j0 + kMid} + h t): the series in v
-    // shifted to v0 = j0 + kMid - P/2 by repeated synthetic division (FP64),
-    // then evaluated by Horner in FP32 at t = i - kMid, |h t| <= 16 / P.
-    // Rows of more than 128 lanes have over 2,000 pixels: there the terms past
-    // the sixth add at most 1e-10 of the continuum's largest value (the
-    // seventh derivative of a degree-10 polynomial by Markov's bound).
-    constexpr int NC = BLOCK == 128 ? ND : (ND < 7 ? ND : 7);
+    constexpr int NC = expansion_terms(BLOCK, ND);
     float cf[NC];
-    {
-      double a[ND];
-#pragma unroll
-      for (int n = 0; n < ND; ++n) a[n] = sBd[n];
-      const double v0 = (double)(j0 + kMid) - 0.5 * (double)P;
-#pragma unroll
-      for (int k = 0; k < ND - 1 && k < NC; ++k)
-#pragma unroll
-        for (int n = ND - 2; n >= k; --n) a[n] = fma(v0, a[n + 1], a[n]);
-#pragma unroll
-      for (int n = 0; n < NC; ++n) cf[n] = (float)a[n];
-    }
+    expand_continuum<ND, NC>(sBd, j0, P, cf);
     auto residual = [&](auto inside) {
 #pragma unroll
       for (int i = 0; i < kNPL; ++i) {

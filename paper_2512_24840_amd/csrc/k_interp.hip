@@ -27,39 +27,6 @@ struct IntC {
   static constexpr int value = V;
 };
 
-// Feature row t of spectrum s: t = 0 is phi(u), t = 1..3 is d phi / d u_t.
-__device__ inline void feature_row(const float *u, int t, float *out) {
-  const float x = u[0], y = u[1], z = u[2];
-  if (t == 0) {
-    features(x, y, z, out);
-  } else {
-    float d[3][kNB];
-    feature_derivs(x, y, z, d);
-    // selects, not an indexed load: keeps d in registers
-#pragma unroll
-    for (int k = 0; k < kNB; ++k) out[k] = t == 1 ? d[0][k] : (t == 2 ? d[1][k] : d[2][k]);
-  }
-}
-
-// The same row over the three emulator classes: entry 20 q + k is
-// w_q phi_k, and its derivative rows carry d w_q / d u1 phi_k as well.
-__device__ inline void feature_row_classes(const Geometry &g, const float *u, int t, float *out) {
-  const float x = u[0], y = u[1], z = u[2];
-  float phi[kNB], r[kNB], d[3][kNB];
-  features(x, y, z, phi);
-  feature_derivs(x, y, z, d);
-#pragma unroll
-  for (int k = 0; k < kNB; ++k)
-    r[k] = t == 0 ? phi[k] : (t == 1 ? d[0][k] : (t == 2 ? d[1][k] : d[2][k]));
-  float w[kMaxClasses], dw[kMaxClasses];
-  class_weights(g, x, w, dw);
-#pragma unroll
-  for (int q = 0; q < kMaxClasses; ++q)
-#pragma unroll
-    for (int k = 0; k < kNB; ++k)
-      out[kNB * q + k] = t == 1 ? fmaf(dw[q], phi[k], w[q] * r[k]) : w[q] * r[k];
-}
-
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef unsigned short ushort8 __attribute__((ext_vector_type(8)));
 

@@ -35,7 +35,7 @@ int dev_fail(hipError_t e, const char *where) {
 struct Workspace {
   int device = 0;
   hipStream_t stream = nullptr;
-  size_t cap_B = 0, cap_ow = 0, cap_fp = 0, cap_fbar = 0, cap_basis = 0, cap_hist = 0, cap_lm = 0;
+  size_t cap_B = 0, cap_ow = 0, cap_fp = 0, cap_fbar = 0, cap_basis = 0, cap_hist = 0;
   size_t cap_tsplit = 0;  // entries of the transposed BF16 split basis
   size_t cap_order = 0;
   int *order = nullptr;     // [B] active list of the stopping rules, then its length
@@ -44,7 +44,6 @@ struct Workspace {
   size_t cap_model = 0;
   float *model = nullptr;  // [B][P] model for the Clean updates
   State s{};
-  lasp::LmState lm{};
   // a chunk of plain Adam steps as one HIP graph (lasp_fit_group), with the
   // bytes of the arguments it was captured with
   hipStream_t cap_st = nullptr;  // capture only: nothing runs on it
@@ -76,11 +75,6 @@ void free_ws(Workspace *w) {
                   s.chi2,     s.basis,    s.basis_hi, s.basis_lo, s.basis_thi, s.basis_tlo};
   for (void *p : ptrs)
     if (p) (void)hipFree(p);
-  lasp::LmState &l = w->lm;
-  void *lptrs[] = {l.normal, l.lambda, l.chi2_trial, l.step_inf, l.u_trial, l.st_trial,
-                   l.need_jac, l.flags};
-  for (void *p : lptrs)
-    if (p) (void)hipFree(p);
   if (w->model) (void)hipFree(w->model);
   w->model = nullptr;
   w->cap_model = 0;
@@ -99,8 +93,7 @@ void free_ws(Workspace *w) {
   if (w->cap_st) (void)hipStreamDestroy(w->cap_st);
   w->cap_st = nullptr;
   w->s = State{};
-  w->lm = lasp::LmState{};
-  w->cap_B = w->cap_ow = w->cap_fp = w->cap_fbar = w->cap_basis = w->cap_hist = w->cap_lm = 0;
+  w->cap_B = w->cap_ow = w->cap_fp = w->cap_fbar = w->cap_basis = w->cap_hist = 0;
   w->cap_tsplit = 0;
 }
 
@@ -109,10 +102,9 @@ void free_ws(Workspace *w) {
 // on).  Earlier work on the stream may still use old buffers, so the stream
 // is synchronised before anything is freed.
 int ensure_buffers(Workspace *w, const Geometry &g, int fp_rows, int hist_w, hipStream_t st,
-                   bool lm = false, bool want_order = false) {
+                   bool want_order = false) {
   const size_t B = (size_t)g.B;
   const size_t need_hist = B * (size_t)hist_w;
-  const size_t need_lm = lm ? B : 0;
   const size_t need_ow = B * lasp::kNPL * g.block;
   const size_t need_fp = B * fp_rows * g.ldF;
   const size_t need_fbar = B * g.ldF;
@@ -122,7 +114,7 @@ int ensure_buffers(Workspace *w, const Geometry &g, int fp_rows, int hist_w, hip
   const bool regrow = B > w->cap_B || need_ow > w->cap_ow || need_fp > w->cap_fp ||
                       need_fbar > w->cap_fbar || need_basis > w->cap_basis ||
                       need_tsplit > w->cap_tsplit || need_order > w->cap_order ||
-                      need_hist > w->cap_hist || need_lm > w->cap_lm || !w->s.u;
+                      need_hist > w->cap_hist || !w->s.u;
   if (!regrow) return LASP_OK;
   hipError_t e = hipStreamSynchronize(st);
   if (e != hipSuccess) return dev_fail(e, "hipStreamSynchronize");
@@ -147,23 +139,6 @@ int ensure_buffers(Workspace *w, const Geometry &g, int fp_rows, int hist_w, hip
   }
   if (r == hipSuccess && need_hist > 0) r = grow(s.lhist, w->cap_hist, need_hist);
   if (r == hipSuccess && need_order > 0) r = grow(w->order, w->cap_order, need_order);
-  if (r == hipSuccess && need_lm > w->cap_lm) {
-    lasp::LmState &l = w->lm;
-    const size_t cl = w->cap_lm;
-    size_t a1 = cl, a2 = cl, a3 = cl, a4 = cl, a5 = cl, a6 = cl, a7 = cl, a8 = cl;
-    r = grow(l.normal, a1, need_lm * lasp::kNormalStride);
-    if (r == hipSuccess) r = grow(l.lambda, a2, need_lm);
-    if (r == hipSuccess) r = grow(l.chi2_trial, a3, need_lm);
-    if (r == hipSuccess) r = grow(l.step_inf, a4, need_lm);
-    if (r == hipSuccess) r = grow(l.u_trial, a5, need_lm * lasp::kNP);
-    if (r == hipSuccess) r = grow(l.st_trial, a6, need_lm);
-    if (r == hipSuccess) r = grow(l.need_jac, a7, need_lm);
-    if (r == hipSuccess) r = grow(l.flags, a8, need_lm + 1);
-    if (r == hipSuccess) {
-      l.active = l.flags + need_lm;
-      w->cap_lm = need_lm;
-    }
-  }
   if (r == hipSuccess) r = grow(s.ow, w->cap_ow, need_ow);
   if (r == hipSuccess) r = grow(s.fp, w->cap_fp, need_fp);
   if (r == hipSuccess) r = grow(s.fbar, w->cap_fbar, need_fbar);
@@ -190,7 +165,7 @@ int ensure_buffers(Workspace *w, const Geometry &g, int fp_rows, int hist_w, hip
 }
 
 int get_workspace(const Geometry &g, int fp_rows, int hist_w, hipStream_t st, Workspace **out,
-                  bool lm = false, bool want_order = false) {
+                  bool want_order = false) {
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return dev_fail(e, "hipGetDevice");
@@ -203,7 +178,7 @@ int get_workspace(const Geometry &g, int fp_rows, int hist_w, hipStream_t st, Wo
     w->stream = st;
     g_ws[key] = w;
   }
-  int rc = ensure_buffers(w, g, fp_rows, hist_w, st, lm, want_order);
+  int rc = ensure_buffers(w, g, fp_rows, hist_w, st, want_order);
   if (rc) return rc;
   *out = w;
   return LASP_OK;
@@ -443,14 +418,21 @@ void prof_drain() {
 
 // Steps between two compactions of the active list (stopping rules on).
 constexpr int kCompactEvery = 16;
-// Polish iterations between two counts of the spectra still iterating.
-constexpr int kLmCheckEvery = 4;
 
 #define LASP_CHECK(call, what)                 \
   do {                                         \
     hipError_t e_ = (call);                    \
     if (e_ != hipSuccess) return dev_fail(e_, what); \
   } while (0)
+
+lasp::CovArgs cov_args(const lasp_opts *o) {
+  lasp::CovArgs ca{};
+  for (int t = 0; t < lasp::kNP; ++t) {
+    ca.lo[t] = o->box_lo[t];
+    ca.hi[t] = o->box_hi[t];
+  }
+  return ca;
+}
 
 // Launch sequence of a forward evaluation at fixed u on the buffers of s
 // (fp rows: 4 when the Jacobian or covariance is wanted, else 1).  The
@@ -485,9 +467,10 @@ int forward_enqueue(const Geometry &g, State s, const float *obs, const float *i
     LASP_TIMED(LASP_K_INTERP_FWD, st);
     LASP_CHECK(lasp::launch_interp_fwd(g, s, rows4 ? 1 : 0, bf16, st), "interpolator contraction");
   }
-  {
+  lasp::OneShot os{obs, ivar, opts->weight_quantile, 0, out_J};
+  if (!rows4 || out_grad) {
     LASP_TIMED(LASP_K_FUSED, st);
-    const lasp::OneShot os{obs, ivar, opts->weight_quantile, rows4 ? 1 : 0, out_J};
+    os.write_ow = rows4 ? 1 : 0;
     LASP_CHECK(lasp::launch_fused_oneshot(g, s, out_grad ? 1 : 0, out_model, os, st), "fused pass");
   }
   if (out_grad) {
@@ -496,8 +479,17 @@ int forward_enqueue(const Geometry &g, State s, const float *obs, const float *i
   }
   if (rows4) {
     LASP_TIMED(LASP_K_COV, st);
-    LASP_CHECK(lasp::launch_cov(g, s, opts->box_lo, opts->box_hi, out_cov, out_jac, nullptr, nullptr, st),
-               "covariance / model Jacobian");
+    lasp::CovArgs ca = cov_args(opts);
+    ca.out_jac = out_jac;
+    ca.out_cov = out_cov;
+    if (out_grad) {  // the fused pass has prepared and evaluated the spectra
+      LASP_CHECK(lasp::launch_cov(g, s, ca, st), "covariance / model Jacobian");
+    } else {
+      ca.os = os;
+      ca.set_status = 1;
+      ca.model_out = out_model;
+      LASP_CHECK(lasp::launch_cov_oneshot(g, s, ca, st), "covariance / model Jacobian");
+    }
   }
   return LASP_OK;
 }
@@ -727,7 +719,7 @@ int lasp_fit_group(const float *obs, const float *ivar, const double *wave_grid,
   // several emulator classes: the work list also groups the spectra by Teff
   // regime (tiles of one regime skip the other classes' products)
   const bool regimes = g.n_classes > 1;
-  rc = get_workspace(g, (out_cov || polish) ? 4 : 1, W, st, &w, polish > 0, regimes);
+  rc = get_workspace(g, (out_cov || polish) ? 4 : 1, W, st, &w, regimes);
   if (rc) return rc;
   if (ce > 0) {
     const size_t need = (size_t)g.B * g.P;
@@ -761,7 +753,7 @@ int lasp_fit_group(const float *obs, const float *ivar, const double *wave_grid,
   }
   const lasp::AdamCfg adam{opts->lr, opts->beta1, opts->beta2, opts->eps, W, opts->stop_tol};
   s.fp_stride = g.ldF;
-  if ((W > 0 || polish > 0) && !w->h_active) {
+  if (W > 0 && !w->h_active) {
     hipError_t e = hipHostMalloc((void **)&w->h_active, 2 * sizeof(int));
     for (int k = 0; e == hipSuccess && k < 2; ++k)
       e = hipEventCreateWithFlags(&w->ev[k], hipEventDisableTiming);
@@ -831,51 +823,22 @@ int lasp_fit_group(const float *obs, const float *ivar, const double *wave_grid,
   s.n_active = nullptr;
   if (polish > 0) {
     // Levenberg-Marquardt polish from the Adam end point
-    const lasp::LmState lm = w->lm;
-    State trial = s;
-    trial.u = lm.u_trial;
-    trial.chi2 = lm.chi2_trial;
-    trial.status = lm.st_trial;
-    trial.fp_stride = g.ldF;
-    LASP_CHECK(lasp::launch_lm_init(g, lm, st), "polish init");
-    for (int it = 0; it < polish; ++it) {
-      s.fp_stride = 4 * g.ldF;
-      LASP_CHECK(lasp::launch_interp_fwd(g, s, 1, bf16, st), "interpolator contraction");
-      {
-        LASP_TIMED(LASP_K_COV, st);
-        LASP_CHECK(lasp::launch_cov(g, s, opts->box_lo, opts->box_hi, nullptr, nullptr, lm.normal,
-                                    lm.need_jac, st),
-                   "normal equations");
-      }
-      LASP_CHECK(lasp::launch_lm_solve(g, s, lm, st), "polish step");
-      LASP_CHECK(lasp::launch_interp_fwd(g, trial, 0, bf16, st), "interpolator contraction");
-      LASP_CHECK(lasp::launch_fused(g, trial, 0, nullptr, 1, st), "fused pass");
-      LASP_CHECK(lasp::launch_lm_accept(g, s, lm, it == polish - 1, st), "polish accept");
-      if ((it + 1) % kLmCheckEvery == 0 && it + 1 < polish) {
-        // once every spectrum has stopped the remaining iterations change
-        // nothing: the host reads the count of kLmCheckEvery iterations
-        // earlier (the device is still working through the ones since) and
-        // stops enqueuing
-        const int slot = ((it + 1) / kLmCheckEvery) & 1;
-        LASP_CHECK(lasp::launch_lm_active(g, lm, st), "polish count");
-        LASP_CHECK(hipMemcpyAsync(w->h_active + slot, lm.active, sizeof(int),
-                                  hipMemcpyDeviceToHost, st),
-                   "polish count");
-        LASP_CHECK(hipEventRecord(w->ev[slot], st), "polish count event");
-        if (it + 1 >= 2 * kLmCheckEvery) {
-          LASP_CHECK(hipEventSynchronize(w->ev[slot ^ 1]), "polish count wait");
-          if (w->h_active[slot ^ 1] == 0) break;
-        }
-      }
-    }
+    LASP_TIMED(LASP_K_COV, st);
+    s.fp_stride = 4 * g.ldF;
+    lasp::CovArgs ca = cov_args(opts);
+    ca.last = polish;
+    LASP_CHECK(lasp::launch_lm(g, s, ca, st), "polish");
   }
   s.fp_stride = out_cov ? 4 * g.ldF : g.ldF;
   LASP_CHECK(lasp::launch_interp_fwd(g, s, out_cov ? 1 : 0, bf16, st), "interpolator contraction");
-  LASP_CHECK(lasp::launch_fused(g, s, 0, nullptr, 1, st), "fused pass");
   if (out_cov) {
     LASP_TIMED(LASP_K_COV, st);
-    LASP_CHECK(lasp::launch_cov(g, s, opts->box_lo, opts->box_hi, out_cov, nullptr, nullptr, nullptr, st),
-               "covariance");
+    lasp::CovArgs ca = cov_args(opts);
+    ca.set_status = 1;
+    ca.out_cov = out_cov;
+    LASP_CHECK(lasp::launch_cov(g, s, ca, st), "covariance");
+  } else {
+    LASP_CHECK(lasp::launch_fused(g, s, 0, nullptr, 1, st), "fused pass");
   }
   {
     LASP_TIMED(LASP_K_FINALIZE, st);
@@ -1056,7 +1019,7 @@ int lasp_pool_create(const double *wave_grid, const float *basis, const lasp_opt
     delete p;
     return dev_fail(e, "hipGetDevice");
   }
-  rc = ensure_buffers(&p->w, g, 4, opts->stop_window, p->st, false, true);
+  rc = ensure_buffers(&p->w, g, 4, opts->stop_window, p->st, true);
   if (!rc) {
     e = hipMemsetAsync(p->w.s.target, 0, sizeof(int) * g.B, p->st);
     if (e == hipSuccess) e = hipMemsetAsync(p->w.s.t, 0, sizeof(int) * g.B, p->st);
@@ -1149,12 +1112,14 @@ int lasp_pool_finish(lasp_pool *p, int32_t slot0, int32_t count, float *out_para
   s.fp_stride = rows * g.ldF;
   LASP_CHECK(lasp::launch_interp_fwd(g, s, out_cov ? 1 : 0, p->bf16, p->st),
              "interpolator contraction");
-  LASP_CHECK(lasp::launch_fused(g, s, 0, nullptr, 1, p->st), "fused pass");
   if (out_cov) {
     LASP_TIMED(LASP_K_COV, p->st);
-    LASP_CHECK(lasp::launch_cov(g, s, p->opts.box_lo, p->opts.box_hi, out_cov, nullptr, nullptr, nullptr,
-                                p->st),
-               "covariance");
+    lasp::CovArgs ca = cov_args(&p->opts);
+    ca.set_status = 1;
+    ca.out_cov = out_cov;
+    LASP_CHECK(lasp::launch_cov(g, s, ca, p->st), "covariance");
+  } else {
+    LASP_CHECK(lasp::launch_fused(g, s, 0, nullptr, 1, p->st), "fused pass");
   }
   LASP_TIMED(LASP_K_FINALIZE, p->st);
   LASP_CHECK(lasp::launch_finalize(g, s, p->opts.box_lo, p->opts.box_hi, out_params, status,
@@ -1175,7 +1140,7 @@ int lasp_pool_resize(lasp_pool *p, int32_t capacity, int32_t keep) {
   Workspace nw;
   nw.device = p->device;
   nw.stream = p->st;
-  int rc = ensure_buffers(&nw, g, 4, W, p->st, false, true);
+  int rc = ensure_buffers(&nw, g, 4, W, p->st, true);
   if (rc) return rc;
   const State &a = p->w.s;
   const State &b = nw.s;

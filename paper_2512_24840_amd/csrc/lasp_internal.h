@@ -39,8 +39,6 @@ constexpr double kLmDecreaseTol = 1e-6;
 constexpr double kLmDropTol = 1e-10;
 constexpr double kLmStepTol = 1e-7;
 constexpr double kLmLambdaMax = 1e10;
-constexpr int kLmDone = 1;
-constexpr int kNormalStride = 32;
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 
@@ -97,19 +95,6 @@ struct State {
   uint16_t *basis_tlo; // [ldF][32] bf16 low part
 };
 
-// Per-spectrum state of the Levenberg-Marquardt polish.
-struct LmState {
-  double *normal;      // [B][kNormalStride] S (25), q (5), chi2 at the current u
-  double *lambda;      // [B] damping
-  double *chi2_trial;  // [B] chi2 at the trial point
-  double *step_inf;    // [B] max |du| of the trial step (NaN: no step)
-  float *u_trial;      // [B][5]
-  uint32_t *st_trial;  // [B] status of the trial evaluation (discarded)
-  int *need_jac;       // [B] 1: normal equations needed at the current u
-  int *flags;          // [B] kLmDone
-  int *active;         // [1] spectra still iterating (k_lm_active)
-};
-
 // Inputs and outputs of the Clean mask kernel.  obs, ivar and model are
 // [B][P] row-major in the units of obs.  With s.ow set, the kernel writes
 // the new weights into the fused pass's (o/w, W w^2) array and n_eff; with
@@ -132,6 +117,17 @@ struct OneShot {
   float quantile;     // of the flux weight
   int write_ow;       // 1: leave (o/w, W w^2) in s.ow for a later kernel
   float *J;           // optional [B]
+};
+
+// Arguments of the covariance kernel.
+struct CovArgs {
+  double lo[kNP], hi[kNP];  // normalisation box
+  OneShot os;               // one-shot evaluation: inputs and J (write_ow unused)
+  int set_status;           // 1: write chi2 and the evaluation's status
+  float *model_out;         // optional [B][P]
+  float *out_jac;           // optional [B][5][P]
+  double *out_cov;          // optional [B][5][5]
+  int last;                 // polish: iterations at most
 };
 
 struct AdamCfg {
@@ -183,17 +179,14 @@ hipError_t launch_finalize(const Geometry &g, const State &s, const double *box_
                            double *chi2_out, int32_t *steps_out, hipStream_t st);
 hipError_t launch_progress(const Geometry &g, const State &s, int32_t *steps, int32_t *done,
                            hipStream_t st);
-// Covariance, model Jacobian and/or Gauss-Newton normal equations
-// (out_normal [B][kNormalStride]: S row-major [25], q [5], chi2) for the
-// spectra with active[spec] != 0 (every spectrum when active is NULL).
-hipError_t launch_cov(const Geometry &g, const State &s, const double *box_lo, const double *box_hi,
-                      double *out_cov, float *out_jac, double *out_normal, const int *active,
-                      hipStream_t st);
-hipError_t launch_lm_init(const Geometry &g, const LmState &lm, hipStream_t st);
-hipError_t launch_lm_solve(const Geometry &g, const State &s, const LmState &lm, hipStream_t st);
-hipError_t launch_lm_active(const Geometry &g, const LmState &lm, hipStream_t st);
-hipError_t launch_lm_accept(const Geometry &g, const State &s, const LmState &lm, int last,
-                            hipStream_t st);
+// Evaluation with covariance and/or model Jacobian (s.fp: four rows per
+// spectrum): of prepared spectra, or preparing them from ca.os.
+hipError_t launch_cov(const Geometry &g, const State &s, const CovArgs &ca, hipStream_t st);
+hipError_t launch_cov_oneshot(const Geometry &g, const State &s, const CovArgs &ca,
+                              hipStream_t st);
+// Levenberg-Marquardt polish of prepared spectra from s.u (s.fp: scratch of
+// four rows per spectrum), each until its own stop or ca.last iterations.
+hipError_t launch_lm(const Geometry &g, const State &s, const CovArgs &ca, hipStream_t st);
 hipError_t launch_clean(const Geometry &g, const CleanArgs &a, hipStream_t st);
 hipError_t launch_resample(const float *src, int n_rows, int n_src, int64_t ld_src, double lam0,
                            double dlam, float *out, int n_out, int64_t ld_out, double lg0,
@@ -202,6 +195,20 @@ bool fused_supported(int block, int nd);
 // Sets the calling thread's lasp_last_error() message; returns code.
 int set_error(int code, const char *msg);
 size_t fused_smem_bytes(const Geometry &g);
+
+// [x^n] T_k(x) for k, n <= 10, from T_k = 2x T_{k-1} - T_{k-2}.
+struct ChebPow {
+  int c[11][11];
+};
+constexpr ChebPow make_cheb_pow() {
+  ChebPow t{};
+  t.c[0][0] = 1;
+  t.c[1][1] = 1;
+  for (int k = 2; k < 11; ++k)
+    for (int n = 0; n <= k; ++n) t.c[k][n] = (n > 0 ? 2 * t.c[k - 1][n - 1] : 0) - t.c[k - 2][n];
+  return t;
+}
+constexpr ChebPow kChebPow = make_cheb_pow();
 
 // ---- Nodes of the continuum moments ---------------------------------------
 constexpr int kMid = kNPL / 2;  // a lane's middle pixel: local expansions are about j0 + kMid
@@ -324,6 +331,39 @@ __device__ inline void feature_derivs(float x, float y, float z, float (*d)[kNB]
   d[1][17] = 2.f * y * z; d[2][17] = y * y;
   d[1][18] = z * z; d[2][18] = 2.f * y * z;
   d[2][19] = 3.f * z * z;
+}
+
+// Feature row t of spectrum s: t = 0 is phi(u), t = 1..3 is d phi / d u_t.
+__device__ inline void feature_row(const float *u, int t, float *out) {
+  const float x = u[0], y = u[1], z = u[2];
+  if (t == 0) {
+    features(x, y, z, out);
+  } else {
+    float d[3][kNB];
+    feature_derivs(x, y, z, d);
+    // selects, not an indexed load: keeps d in registers
+#pragma unroll
+    for (int k = 0; k < kNB; ++k) out[k] = t == 1 ? d[0][k] : (t == 2 ? d[1][k] : d[2][k]);
+  }
+}
+
+// The same row over the three emulator classes: entry 20 q + k is
+// w_q phi_k, and its derivative rows carry d w_q / d u1 phi_k as well.
+__device__ inline void feature_row_classes(const Geometry &g, const float *u, int t, float *out) {
+  const float x = u[0], y = u[1], z = u[2];
+  float phi[kNB], r[kNB], d[3][kNB];
+  features(x, y, z, phi);
+  feature_derivs(x, y, z, d);
+#pragma unroll
+  for (int k = 0; k < kNB; ++k)
+    r[k] = t == 0 ? phi[k] : (t == 1 ? d[0][k] : (t == 2 ? d[1][k] : d[2][k]));
+  float w[kMaxClasses], dw[kMaxClasses];
+  class_weights(g, x, w, dw);
+#pragma unroll
+  for (int q = 0; q < kMaxClasses; ++q)
+#pragma unroll
+    for (int k = 0; k < kNB; ++k)
+      out[kNB * q + k] = t == 1 ? fmaf(dw[q], phi[k], w[q] * r[k]) : w[q] * r[k];
 }
 
 // Butterfly reduce-scatter of N per-lane values over a 64-lane wave.
@@ -835,6 +875,152 @@ __device__ inline void lane_moments(int j0, int P, const float (&fpp)[kNPL],
   for (int k = 1; k < ND; ++k) acc[ND - 1 + k] = s.q[k];
 #pragma unroll
   for (int k = 0; k < ND; ++k) acc[2 * ND - 1 + k] = s.rr[k];
+}
+
+// Normal equations A b = r of the continuum (A_mn = (nu_{m+n} + nu_|m-n|)/2)
+// from the moments nu_0..nu_D, q_1..q_D, r_0..r_D (nu_{D+k} = 2 q_k -
+// nu_{D-k}), solved in FP64 by one wave, lane i holding row i.
+
+// nu_0 .. nu_2D mirrored about index D (sNu[D + l] = sNu[D - l] = nu_l), so
+// that row i reads nu_{i+n} and nu_{|i-n|} at fixed offsets from sNu + i.
+template <int ND>
+__device__ inline void mirror_moments(const double *sMom, double *sNu, int lane) {
+  constexpr int D = ND - 1, NNU = 2 * ND - 1;
+  const int l = min(lane, NNU - 1);
+  const double lo = sMom[l], hi = sMom[l <= D ? l : 2 * D - l];
+  const double nu = l <= D ? lo : fma(2.0, lo, -hi);
+  if (lane < NNU) sNu[D + lane] = nu;
+  if (lane >= 1 && lane <= D) sNu[D - lane] = nu;
+}
+
+// Gauss-Jordan on NC - ND right-hand sides without scaling the pivot rows:
+// row k stays as it is and every other row loses its column-k entry; the
+// solutions are rhs[c] / diag of row i, diag its own entry.  The pivots are
+// those of the scaled form.  Returns whether all of them are positive and
+// finite.
+template <int ND, int NC>
+__device__ inline bool eliminate(const double (&rows)[NC], int lane, double (&rhs)[NC - ND],
+                                 double &diag) {
+#pragma clang fp contract(off)
+  double a[NC];  // a local copy: stays in registers
+#pragma unroll
+  for (int n = 0; n < NC; ++n) a[n] = rows[n];
+  bool ok = true;
+#pragma unroll
+  for (int k = 0; k < ND; ++k) {
+    double piv[NC];
+#pragma unroll
+    for (int n = k; n < NC; ++n) piv[n] = read_lane(a[n], k);
+    ok = ok && (piv[k] > 0.0) && isfinite(piv[k]);
+    // 1 / pivot: the hardware estimate and two Newton steps
+    double rp = __builtin_amdgcn_rcp(piv[k]);
+    rp = fma(rp, fma(-piv[k], rp, 1.0), rp);
+    rp = fma(rp, fma(-piv[k], rp, 1.0), rp);
+    const double f = lane == k ? 0.0 : a[k] * rp;
+#pragma unroll
+    for (int n = k + 1; n < NC; ++n) a[n] = fma(-f, piv[n], a[n]);
+  }
+  double dg = a[0];
+#pragma unroll
+  for (int n = 1; n < ND; ++n) dg = lane == n ? a[n] : dg;
+  diag = dg;
+#pragma unroll
+  for (int c = 0; c < NC - ND; ++c) rhs[c] = a[ND + c];
+  return ok;
+}
+
+// Solves for b and leaves the continuum in sBd as a power series in the pixel
+// offset v = j - P/2 from the row's centre: x_j = h v with h = 2 / P, so
+// C = sum_n m_n h^n v^n with m_n = sum_k b_k [x^n] T_k.  b goes through LDS to
+// every lane of the wave, the coefficients m_n h^n back to LDS.  sNu: 3 D + 1
+// doubles of scratch, left holding the mirrored moments; sBd: 32 doubles.
+template <int ND>
+__device__ inline bool solve_continuum(const double *sMom, double *sNu, double *sBd,
+                                       const Geometry &g, int lane) {
+#pragma clang fp contract(off)
+  constexpr int D = ND - 1, NNU = 2 * ND - 1;
+  mirror_moments<ND>(sMom, sNu, lane);
+  // lanes past row D repeat row D; only rows 0..D are read or stored
+  const bool own = lane < ND;
+  double a[ND + 1];
+  a[ND] = sMom[NNU + min(lane, ND - 1)];
+  wave_lds_sync();
+  {
+    const double *nr = sNu + min(lane, ND - 1);
+#pragma unroll
+    for (int n = 0; n < ND; ++n) a[n] = 0.5 * (nr[D + n] + nr[D - n]);
+  }
+  double b[1], dg;
+  const bool ok = eliminate<ND, ND + 1>(a, lane, b, dg);
+  if (own) sBd[16 + lane] = ok ? b[0] / dg : 0.0;
+  wave_lds_sync();
+  double bk[ND];
+#pragma unroll
+  for (int k = 0; k < ND; ++k) bk[k] = sBd[16 + k];
+  double mm[ND];
+#pragma unroll
+  for (int n = 0; n < ND; ++n) {
+    double m = 0.0;
+#pragma unroll
+    for (int k = n; k < ND; k += 2) m = fma(bk[k], (double)kChebPow.c[k][n], m);
+    mm[n] = m * g.hpow[n];
+  }
+  if (lane == 0) {
+#pragma unroll
+    for (int n = 0; n < ND; ++n) sBd[n] = mm[n];
+  }
+  return ok;
+}
+
+// Terms of a lane's local expansion.  Rows of more than 128 lanes have over
+// 2,000 pixels: there the terms past the sixth order add at most 1e-10 of the
+// continuum's largest value (the seventh derivative of a degree-10 polynomial
+// by Markov's bound).
+constexpr int expansion_terms(int block, int nd) { return block == 128 || nd < 7 ? nd : 7; }
+
+// Taylor coefficients of t -> C(x_{j0 + kMid} + h t): the series in v shifted
+// to v0 = j0 + kMid - P/2 by repeated synthetic division (FP64), for Horner in
+// FP32 at t = i - kMid, |h t| <= 16 / P.
+template <int ND, int NC>
+__device__ inline void expand_continuum(const double *sBd, int j0, int P, float (&cf)[NC]) {
+  double a[ND];
+#pragma unroll
+  for (int n = 0; n < ND; ++n) a[n] = sBd[n];
+  const double v0 = (double)(j0 + kMid) - 0.5 * (double)P;
+#pragma unroll
+  for (int k = 0; k < ND - 1 && k < NC; ++k)
+#pragma unroll
+    for (int n = ND - 2; n >= k; --n) a[n] = fma(v0, a[n + 1], a[n]);
+#pragma unroll
+  for (int n = 0; n < NC; ++n) cf[n] = (float)a[n];
+}
+
+// Folds one quantity v_i of a lane's pixels onto the nodes: Y[2 c], Y[2 c + 1]
+// at x_mid +- h tau_c, Y[6] at x_mid.
+template <typename V>
+__device__ inline void fold_nodes(V &&v, float (&Y)[kNodes]) {
+#pragma clang fp contract(off)
+  float e[kPairs + 1], o[kPairs];
+  const float v0 = v(kMid);
+#pragma unroll
+  for (int c = 0; c <= kPairs; ++c) e[c] = v0 * kMomentNodes.e[c][0];
+#pragma unroll
+  for (int c = 0; c < kPairs; ++c) o[c] = 0.f;
+#pragma unroll
+  for (int t = 1; t <= kMid; ++t) {
+    const float vp = v(kMid + t), vm = v(kMid - t);
+    const float s = vp + vm, d = vp - vm;
+#pragma unroll
+    for (int c = 0; c <= kPairs; ++c) e[c] = fmaf(kMomentNodes.e[c][t], s, e[c]);
+#pragma unroll
+    for (int c = 0; c < kPairs; ++c) o[c] = fmaf(kMomentNodes.o[c][t], d, o[c]);
+  }
+#pragma unroll
+  for (int c = 0; c < kPairs; ++c) {
+    Y[2 * c] = e[c] + o[c];
+    Y[2 * c + 1] = e[c] - o[c];
+  }
+  Y[kNodes - 1] = e[kPairs];
 }
 
 #endif  // __HIPCC__
