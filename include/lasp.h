@@ -151,17 +151,18 @@ extern "C" {
  *                  e1 <= T <= e2 and T >= e3, a linear blend in Teff across
  *                  (e0, e1) and (e2, e3).  BF16X3 supports one class only.
  *  class_edges     e0 < e1 < e2 < e3 in K (default 4000, 4550, 7000, 9000).
- *  step_graph      1 (default): lasp_fit_group enqueues its Adam steps as
- *                  replays of one HIP graph of 25 steps when no stopping
- *                  rules, no Clean and one emulator class are asked for
- *                  (the steps then launch the same kernels with the same
- *                  arguments) and n_spec <= 4096 (larger groups launch
- *                  long kernels); the graph is captured on first use and kept
- *                  with the call's cached device scratch until the
- *                  geometry, the buffers or the Adam settings change, and
- *                  the results are those of launching each step's kernels
- *                  (0).  Kernel timing (lasp_profile_enable) launches
- *                  them one by one.
+ *  step_graph      1 (default): when no stopping rules, no Clean and one
+ *                  emulator class are asked for, lasp_fit_group takes its
+ *                  Adam steps with fewer launches: an FP32 group of at most
+ *                  1,024 spectra (256 when n_pix > 4,352) in one launch, a
+ *                  workgroup per spectrum; BF16X3 groups and larger ones up
+ *                  to 4,096 spectra as replays of one HIP graph of 25 steps
+ *                  (larger groups launch long kernels).  The graph is
+ *                  captured on first use and kept with the call's cached
+ *                  device scratch until the geometry, the buffers or the
+ *                  Adam settings change.  The results are those of
+ *                  launching each step's kernels (0), bit for bit.  Kernel
+ *                  timing (lasp_profile_enable) launches them one by one.
  */
 typedef struct lasp_opts {
   int32_t n_spec;

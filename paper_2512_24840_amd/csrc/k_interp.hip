@@ -269,17 +269,12 @@ template <int NB>
 __device__ inline void bwd_epilogue(const Geometry &g, const State &s, const AdamCfg &adam,
                                     int do_adam, float *grad_out, int spec, const float *pb) {
   float *u = s.u + (size_t)spec * kNP;
+  float grad[kNP];
   float d[3][kNB];
   feature_derivs(u[0], u[1], u[2], d);
-  float grad[kNP];
   if constexpr (NB == kNB) {
 #pragma unroll
-    for (int a = 0; a < 3; ++a) {
-      float acc = 0.f;
-#pragma unroll
-      for (int k = 1; k < kNB; ++k) acc = fmaf(pb[k], d[a][k], acc);
-      grad[a] = acc;
-    }
+    for (int a = 0; a < 3; ++a) grad[a] = shape_gradient(pb, d[a]);
   } else {
     // d (sum_q w_q phi . Phi-bar_q) / d u_a: the class weights depend on u1
     float phi[kNB], w[kMaxClasses], dw[kMaxClasses];
@@ -337,21 +332,21 @@ __device__ inline void bwd_epilogue(const Geometry &g, const State &s, const Ada
     const int step = s.t[spec] + 1;
     s.t[spec] = step;
     if (adam.stop_window > 0 && step >= s.target[spec]) s.status[spec] |= kStNotConverged;
-    const float bc1 = 1.f - powf(adam.beta1, (float)step);
-    const float bc2 = 1.f - powf(adam.beta2, (float)step);
-    const float step_size = adam.lr / bc1;
-    const float rbc2 = 1.f / sqrtf(bc2);
-    float *m = s.m + (size_t)spec * kNP;
-    float *v = s.v + (size_t)spec * kNP;
+    float *m = s.m + (size_t)spec * kNP, *v = s.v + (size_t)spec * kNP;
+    float ua[kNP], ma[kNP], va[kNP];  // all loads before the first store
 #pragma unroll
     for (int a = 0; a < kNP; ++a) {
-      const float ga = grad[a];
-      const float ma = adam.beta1 * m[a] + (1.f - adam.beta1) * ga;
-      const float va = adam.beta2 * v[a] + (1.f - adam.beta2) * ga * ga;
-      m[a] = ma;
-      v[a] = va;
-      const float denom = sqrtf(va) * rbc2 + adam.eps;
-      u[a] = u[a] - step_size * (ma / denom);
+      ua[a] = u[a];
+      ma[a] = m[a];
+      va[a] = v[a];
+    }
+    const AdamStep as = adam_step(adam, step);
+#pragma unroll
+    for (int a = 0; a < kNP; ++a) {
+      adam_update(adam, as, grad[a], ma[a], va[a], ua[a]);
+      u[a] = ua[a];
+      m[a] = ma[a];
+      v[a] = va[a];
     }
   }
 }
@@ -589,25 +584,55 @@ __global__ __launch_bounds__(512) void k_interp_bwd(Geometry g, State s, AdamCfg
       step(q0, q1, fa, bv);
     }
   };
-  floatx4 acc4 = {0.f, 0.f, 0.f, 0.f};
+  floatx4 acc4[4];   // NB == kNB: rows 16-19
+  floatx16 acc16[2];  // NB == kNB: rows 0-15
   if constexpr (NB == kNB) {
-    // Basis rows 0-15 as one 16-row group of 16x16x4 products; rows 16-19
+    // Basis rows 0-15 as products of four 16x16x1 blocks, one per quarter of
+    // the 16 columns: a lane's float4 is four steps of its block.  Rows 16-19
     // as sixteen 4x4x1 blocks, no zero rows: block b = g + 8 h (lanes 4b ..
     // 4b + 3) takes spectra 4g .. 4g + 3 and the h-th 16 columns of each
     // 32-column stage, so lane l supplies F-bar' of spectrum l & 31 and
-    // basis row 16 + (l & 3), and accumulates spectra 4g + r x row 16 + (l & 3).
+    // basis row 16 + (l & 3), and accumulates spectra 4g + r x row 16 + (l & 3),
+    // each float4 of the 16 columns in an accumulator of its own.
+    //
+    // So an entry of Phi-bar is, per wave, a few chains of fused multiply-adds
+    // over the float4 at one place of every 16 (rows 0-15) or 32 (rows 16-19)
+    // columns, added pairwise: the order in which a workgroup that holds one
+    // spectrum can form it with coalesced loads (the fit kernel does, and its
+    // fits are these bit for bit).  The products' rate is that of 16x16x4:
+    // 65.3 us at 16,384 x 3,900 (64.8 in one chain), 211 at
+    // 65,536 (200), 0.5 % of a pass.  One workgroup per CU
+    // is no worse than two: held to 128 registers the kernel took 66 to 96 us
+    // in several forms, and 73 with the basis rows staged through LDS.
+#pragma unroll
+    for (int rt = 0; rt < 2; ++rt)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc16[rt][r] = 0.f;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) acc4[q] = floatx4{0.f, 0.f, 0.f, 0.f};
+    auto step16 = [&](const float4 (&a)[2], const float4 &b) {
+#pragma unroll
+      for (int rt = 0; rt < 2; ++rt) acc16[rt] = __builtin_amdgcn_mfma_f32_16x16x1f32(a[rt].x, b.x, acc16[rt], 0, 0, 0);
+#pragma unroll
+      for (int rt = 0; rt < 2; ++rt) acc16[rt] = __builtin_amdgcn_mfma_f32_16x16x1f32(a[rt].y, b.y, acc16[rt], 0, 0, 0);
+#pragma unroll
+      for (int rt = 0; rt < 2; ++rt) acc16[rt] = __builtin_amdgcn_mfma_f32_16x16x1f32(a[rt].z, b.z, acc16[rt], 0, 0, 0);
+#pragma unroll
+      for (int rt = 0; rt < 2; ++rt) acc16[rt] = __builtin_amdgcn_mfma_f32_16x16x1f32(a[rt].w, b.w, acc16[rt], 0, 0, 0);
+    };
     const int hh = lane >> 5, r4 = lane & 31, j4 = lane & 3;
     const float *b4 = s.basis + (size_t)(16 + j4) * g.ldF;
     const float *fb4row = s.fbar + (size_t)work_spec(s, s0 + r4 < count ? s0 + r4 : s0) * g.ldF;
     float *stg = sbuf + wave * kStage;
-    const float *rp[4];
+    uint32_t ro[4];  // row offsets in float4 (B ldF / 4, below 2^32)
     bool rv[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       const int ri = 8 * j + (lane >> 3);
       rv[j] = s0 + ri < count;
-      rp[j] = s.fbar + (size_t)work_spec(s, rv[j] ? s0 + ri : s0) * g.ldF + 4 * (lane & 7);
+      ro[j] = (uint32_t)work_spec(s, rv[j] ? s0 + ri : s0) * (uint32_t)(g.ldF / 4) + (lane & 7);
     }
+    const float4 *fb4 = reinterpret_cast<const float4 *>(s.fbar);
     // lanes 0-31 stage basis rows 16-19 of the stage (row 32 + (lane >> 3))
     const float *bs = s.basis + (size_t)(16 + ((lane >> 3) & 3)) * g.ldF + 4 * (lane & 7);
     int c = cb;
@@ -616,7 +641,7 @@ __global__ __launch_bounds__(512) void k_interp_bwd(Geometry g, State s, AdamCfg
       auto fetch = [&](int cc) {
 #pragma unroll
         for (int j = 0; j < 4; ++j)
-          fv[j] = rv[j] ? *reinterpret_cast<const float4 *>(rp[j] + cc) : make_float4(0.f, 0.f, 0.f, 0.f);
+          fv[j] = rv[j] ? fb4[(size_t)ro[j] + cc / 4] : make_float4(0.f, 0.f, 0.f, 0.f);
         fs = lane < 32 ? *reinterpret_cast<const float4 *>(bs + cc) : make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
         for (int u = 0; u < kU; ++u) bv[u] = *reinterpret_cast<const float4 *>(b_ptr[0] + cc + 16 * u + 4 * kq);
@@ -636,21 +661,20 @@ __global__ __launch_bounds__(512) void k_interp_bwd(Geometry g, State s, AdamCfg
         if (c + 64 <= ce) fetch(c + 32);  // next stage
 #pragma unroll
         for (int u = 0; u < kU; ++u) {
-          float4 fa[2], b16[NG];
+          float4 fa[2];
 #pragma unroll
           for (int rt = 0; rt < 2; ++rt)
             fa[rt] = *reinterpret_cast<const float4 *>(stg + (16 * rt + i_row) * kSLd + 16 * u + 4 * kq);
-          b16[0] = bcur[u];
-          step(IntC<0>{}, IntC<1>{}, fa, b16);
+          step16(fa, bcur[u]);
         }
 #pragma unroll
         for (int qq = 0; qq < 4; ++qq) {
           const float4 a4 = *reinterpret_cast<const float4 *>(stg + r4 * kSLd + 16 * hh + 4 * qq);
           const float4 w4 = *reinterpret_cast<const float4 *>(stg + (32 + j4) * kSLd + 16 * hh + 4 * qq);
-          acc4 = __builtin_amdgcn_mfma_f32_4x4x1f32(a4.x, w4.x, acc4, 0, 0, 0);
-          acc4 = __builtin_amdgcn_mfma_f32_4x4x1f32(a4.y, w4.y, acc4, 0, 0, 0);
-          acc4 = __builtin_amdgcn_mfma_f32_4x4x1f32(a4.z, w4.z, acc4, 0, 0, 0);
-          acc4 = __builtin_amdgcn_mfma_f32_4x4x1f32(a4.w, w4.w, acc4, 0, 0, 0);
+          acc4[qq] = __builtin_amdgcn_mfma_f32_4x4x1f32(a4.x, w4.x, acc4[qq], 0, 0, 0);
+          acc4[qq] = __builtin_amdgcn_mfma_f32_4x4x1f32(a4.y, w4.y, acc4[qq], 0, 0, 0);
+          acc4[qq] = __builtin_amdgcn_mfma_f32_4x4x1f32(a4.z, w4.z, acc4[qq], 0, 0, 0);
+          acc4[qq] = __builtin_amdgcn_mfma_f32_4x4x1f32(a4.w, w4.w, acc4[qq], 0, 0, 0);
         }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
@@ -660,16 +684,19 @@ __global__ __launch_bounds__(512) void k_interp_bwd(Geometry g, State s, AdamCfg
     for (; c < ce; c += 16) {  // a 16-column tail: lanes of half 1 add zeros
       float4 fa[2], bv[NG];
       load(IntC<0>{}, IntC<1>{}, c + 4 * kq, fa, bv);
-      step(IntC<0>{}, IntC<1>{}, fa, bv);
+#pragma unroll
+      for (int rt = 0; rt < 2; ++rt)
+        if (!row_ok[rt]) fa[rt] = make_float4(0.f, 0.f, 0.f, 0.f);
+      step16(fa, bv[0]);
 #pragma unroll
       for (int qq = 0; qq < 4; ++qq) {
         float4 a4 = *reinterpret_cast<const float4 *>(fb4row + c + 4 * qq);
         const float4 w4 = *reinterpret_cast<const float4 *>(b4 + c + 4 * qq);
         if (hh) a4 = make_float4(0.f, 0.f, 0.f, 0.f);
-        acc4 = __builtin_amdgcn_mfma_f32_4x4x1f32(a4.x, w4.x, acc4, 0, 0, 0);
-        acc4 = __builtin_amdgcn_mfma_f32_4x4x1f32(a4.y, w4.y, acc4, 0, 0, 0);
-        acc4 = __builtin_amdgcn_mfma_f32_4x4x1f32(a4.z, w4.z, acc4, 0, 0, 0);
-        acc4 = __builtin_amdgcn_mfma_f32_4x4x1f32(a4.w, w4.w, acc4, 0, 0, 0);
+        acc4[qq] = __builtin_amdgcn_mfma_f32_4x4x1f32(a4.x, w4.x, acc4[qq], 0, 0, 0);
+        acc4[qq] = __builtin_amdgcn_mfma_f32_4x4x1f32(a4.y, w4.y, acc4[qq], 0, 0, 0);
+        acc4[qq] = __builtin_amdgcn_mfma_f32_4x4x1f32(a4.z, w4.z, acc4[qq], 0, 0, 0);
+        acc4[qq] = __builtin_amdgcn_mfma_f32_4x4x1f32(a4.w, w4.w, acc4[qq], 0, 0, 0);
       }
     }
   } else {
@@ -702,15 +729,19 @@ __global__ __launch_bounds__(512) void k_interp_bwd(Geometry g, State s, AdamCfg
   }
   __syncthreads();  // every wave is done with its stage: the buffer takes the partial sums
   if constexpr (NB == kNB) {
-    // rows 0-15 from the 16-row group; rows 16-19 from the 4x4 blocks, the
-    // two column halves in columns 16-19 and 20-23
+    // the blocks' sums; rows 16-19 have the two column halves in columns
+    // 16-19 and 20-23
 #pragma unroll
     for (int rt = 0; rt < 2; ++rt)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) red[wave][16 * rt + 4 * kq + r][i_row] = acc[rt][0][r];
+      for (int r = 0; r < 4; ++r)
+        red[wave][16 * rt + 4 * kq + r][i_row] =
+            (acc16[rt][r] + acc16[rt][4 + r]) + (acc16[rt][8 + r] + acc16[rt][12 + r]);
     const int g4 = (lane >> 2) & 7;
 #pragma unroll
-    for (int r = 0; r < 4; ++r) red[wave][4 * g4 + r][16 + (lane & 3) + 4 * (lane >> 5)] = acc4[r];
+    for (int r = 0; r < 4; ++r)
+      red[wave][4 * g4 + r][16 + (lane & 3) + 4 * (lane >> 5)] =
+          (acc4[0][r] + acc4[1][r]) + (acc4[2][r] + acc4[3][r]);
   } else {
 #pragma unroll
     for (int rt = 0; rt < 2; ++rt)

@@ -566,6 +566,14 @@ size_t carve_forward_state(const Geometry &g, int fp_rows, int bf16, unsigned ch
 constexpr int kGraphSteps = 25;
 constexpr int kGraphMaxSpectra = 4096;
 
+// Largest group that is fitted by one workgroup per spectrum (launch_fit): two
+// rounds of the workgroups that fit the chip at once (512 of 256 threads, 1,024
+// of 128, 256 of 512), one where a second round does not pay.  Per step against
+// the step graph: 3,900 px (256 threads) 1,024 spectra 49 against 61 us, 2,048
+// 95 against 82; 1,550 px (128) 1,024 23 against 43, 2,048 55 against 51;
+// 7,800 px in three arms (512) 256 about 48 against 87, 700 133 against 124.
+int fit_max_spectra(const Geometry &g) { return g.block == 512 ? 256 : 1024; }
+
 // Enqueues chunks x kGraphSteps plain Adam steps (interpolator contraction,
 // fused pass, adjoint contraction + Adam; no stopping rules, one emulator
 // class, no Clean) on st as replays of one HIP graph.  The graph is captured
@@ -760,8 +768,11 @@ int lasp_fit_group(const float *obs, const float *ivar, const double *wave_grid,
     if (e != hipSuccess) return dev_fail(e, "active-list events");
   }
   int it0 = 0;
-  if (opts->step_graph && W == 0 && !regimes && ce == 0 && g_prof_mask.load() == 0 &&
-      n_steps >= kGraphSteps && g.B <= kGraphMaxSpectra) {
+  const bool plain = opts->step_graph && W == 0 && !regimes && ce == 0 && g_prof_mask.load() == 0;
+  if (plain && !bf16 && n_steps > 0 && g.B <= fit_max_spectra(g)) {
+    LASP_CHECK(lasp::launch_fit(g, s, adam, n_steps, st), "fit");
+    it0 = n_steps;
+  } else if (plain && n_steps >= kGraphSteps && g.B <= kGraphMaxSpectra) {
     // the plain path launches the same three kernels with the same
     // arguments at every step: whole chunks replay one cached graph (not
     // while kernels are being timed, which brackets each launch)

@@ -41,6 +41,7 @@ constexpr double kLmStepTol = 1e-7;
 constexpr double kLmLambdaMax = 1e10;
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
+typedef float floatx16 __attribute__((ext_vector_type(16)));
 
 // Geometry shared by every per-step kernel.
 struct Geometry {
@@ -171,6 +172,11 @@ hipError_t launch_fused(const Geometry &g, const State &s, int adjoint, float *m
 // whole status.
 hipError_t launch_fused_oneshot(const Geometry &g, const State &s, int adjoint, float *model_out,
                                 const OneShot &os, hipStream_t st);
+// n_steps Adam steps of every spectrum, one workgroup each (one emulator
+// class, FP32 contractions, no stopping rules): the results of as many
+// launches of the three step kernels, bit for bit.
+hipError_t launch_fit(const Geometry &g, const State &s, const AdamCfg &adam, int n_steps,
+                      hipStream_t st);
 hipError_t launch_interp_bwd(const Geometry &g, const State &s, const AdamCfg *adam,
                              float *grad_out, int bf16x3, hipStream_t st);
 hipError_t launch_split_basis(const Geometry &g, const State &s, hipStream_t st);
@@ -364,6 +370,34 @@ __device__ inline void feature_row_classes(const Geometry &g, const float *u, in
 #pragma unroll
     for (int k = 0; k < kNB; ++k)
       out[kNB * q + k] = t == 1 ? fmaf(dw[q], phi[k], w[q] * r[k]) : w[q] * r[k];
+}
+
+// dJ/du_t (t = 1..3) from Phi-bar and d phi / d u_t (one emulator class).
+__device__ inline float shape_gradient(const float *pb, const float *d) {
+  float acc = 0.f;
+#pragma unroll
+  for (int k = 1; k < kNB; ++k) acc = fmaf(pb[k], d[k], acc);
+  return acc;
+}
+
+// Adam's step number `step` (1, 2, ...): what all parameters share, and one
+// parameter's update.
+struct AdamStep {
+  float step_size, rbc2;
+};
+__device__ inline AdamStep adam_step(const AdamCfg &c, int step) {
+#pragma clang fp contract(off)
+  const float bc1 = 1.f - powf(c.beta1, (float)step);
+  const float bc2 = 1.f - powf(c.beta2, (float)step);
+  return AdamStep{c.lr / bc1, 1.f / sqrtf(bc2)};
+}
+__device__ inline void adam_update(const AdamCfg &c, const AdamStep &s, float grad, float &m,
+                                   float &v, float &u) {
+#pragma clang fp contract(off)
+  m = fmaf(c.beta1, m, (1.f - c.beta1) * grad);
+  v = fmaf(c.beta2, v, (1.f - c.beta2) * grad * grad);
+  const float denom = fmaf(sqrtf(v), s.rbc2, c.eps);
+  u = fmaf(-s.step_size, m / denom, u);
 }
 
 // Butterfly reduce-scatter of N per-lane values over a 64-lane wave.

@@ -281,8 +281,8 @@ def fit_group(obs, ivar, wave_grid, basis, init_params, n_steps, *, want_cov=Fal
     clean_every > 0 turns on the Clean mask updates (every clean_every steps,
     at most clean_max times); n_classes = 3 takes a [60, P + 2M] basis of
     three emulator temperature classes blended over the Teff regimes;
-    step_graph=False launches every step's kernels instead of replaying the
-    cached graph of 25 steps (same results)."""
+    step_graph=False launches every step's kernels instead of taking the
+    steps in one launch or from a cached graph (same results)."""
     lib = load()
     B, P = obs.shape
     _dev(obs, "obs", torch.float32, (B, P))
