@@ -15,13 +15,14 @@
 // 2^-16 relative), accumulated in FP32.  In the forward contraction the
 // constant monomial's row (phi_0 = 1) is added in FP32 exactly and only
 // rows 1..19 go through BF16x3.
+#include <algorithm>
+
 #include "lasp_internal.h"
 
 namespace lasp {
 namespace {
 
 constexpr int kFwdTiles = 8;  // 16-pixel tiles per wave in the forward GEMM
-
 template <int V>
 struct IntC {
   static constexpr int value = V;
@@ -112,154 +113,209 @@ __device__ inline void fwd_store(const Geometry &g, const State &s, const float 
   }
 }
 
-// BF16x3 variant of k_interp_fwd (same grid and output layout).
+// Row tiles per workgroup of the forward GEMM, from the rows of the work list:
+// enough that the workgroups are all resident at once (four per CU, by LDS),
+// and the basis entries are read once for them.  3,900 px in FP32, one tile
+// against this rule: 6,000 rows 27.2 and 25.0 us, 20,000 69.0 and 59.6, 65,536
+// 275 and 192; with two tiles (4,096 rows) 21.0 both, so from three on.  The
+// BF16x3 kernel (three workgroups per CU) takes 8 tiles at most: 65,536 rows
+// 273 and 189 us, 208 with 16 tiles.  One tile over fixed slots of which some
+// may be done (no work list), lest the active ones meet in few workgroups, and
+// over three classes, whose basis entries do not fit the registers.
+constexpr int kFwdResident = 1024;
+constexpr int kFwdBf16Tiles = 8;
+__host__ __device__ inline bool fwd_one_tile(const Geometry &g, const State &s) {
+  return g.nb != kNB || (s.target && !s.order);
+}
+__device__ inline int fwd_row_tiles(const Geometry &g, const State &s, int rows, int most) {
+  if (fwd_one_tile(g, s)) return 1;
+  const int rounds = ((rows + 15) / 16 * (int)gridDim.x + kFwdResident - 1) / kFwdResident;
+  return rounds < 3 ? 1 : min(rounds, most);
+}
+
+// BF16x3 variant of k_interp_fwd (same grid and output layout, the basis
+// entries kept over the row tiles as there): 16,384 x 3,900 in 51 us (72).
+// The constant row is one FP32 product on the matrix core, a fused
+// multiply-add of the sum like any other step of its chain.
 __global__ __launch_bounds__(256) void k_interp_fwd_bf16(Geometry g, State s, int rows_per_spec, int skip_done) {
   __shared__ __align__(16) float sT[16 * kFwdLd];
   __shared__ int dst[16];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int rows = work_count(g, s) * rows_per_spec;
-  const int r0 = blockIdx.y * 16;
+  const int row_tiles = fwd_row_tiles(g, s, rows, kFwdBf16Tiles);
+  int r0 = blockIdx.y * 16 * row_tiles;
   if (r0 >= rows) return;  // past the work list (uniform over the block)
-  const int my_row = r0 + (lane & 15);
+  const int r_end = min(rows, r0 + 16 * row_tiles);
   const int kq = lane >> 4;
-  if (skip_done && s.target) {
-    bool any = false;
-    for (int r = 0; r < 16; ++r) {
-      const int row = r0 + r;
-      any = any || (row < rows && slot_active(s, work_spec(s, row / rows_per_spec)));
-    }
-    if (!any) return;
-  }
-  fwd_dst_rows(s, r0, rows, rows_per_spec, dst);
-  bf16x8 b_hi, b_lo;
-  float phi0 = 0.f;
-  {
-    float phi[32];
-#pragma unroll
-    for (int k = 0; k < 32; ++k) phi[k] = 0.f;
-    if (my_row < rows) {
-      const int e = my_row / rows_per_spec;
-      const int t = my_row - e * rows_per_spec;
-      feature_row(s.u + (size_t)work_spec(s, e) * kNP, t, phi);
-    }
-    phi0 = phi[0];
-    phi[0] = 0.f;  // constant row added in FP32 below
-    float sel[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      float v = phi[e];
-#pragma unroll
-      for (int q = 1; q < 4; ++q)
-        if (kq == q) v = phi[8 * q + e];
-      sel[e] = v;
-    }
-    split8(sel, b_hi, b_lo);
-  }
-  // phi_0 of the spectrum whose outputs this lane holds (column j = lane % 16)
   const int cbase = (blockIdx.x * 4 + wave) * (16 * kFwdTiles);
+  bf16x8 a_hi[kFwdTiles], a_lo[kFwdTiles];
+  float a0[kFwdTiles];  // row 0 of the basis, with the lanes of k = 0
+#pragma unroll
   for (int n = 0; n < kFwdTiles; ++n) {
-    const int c0 = cbase + 16 * n;
-    if (c0 >= g.ldF) break;
-    const uint16_t *ah = s.basis_thi + (size_t)(c0 + (lane & 15)) * 32 + 8 * kq;
-    const uint16_t *al = s.basis_tlo + (size_t)(c0 + (lane & 15)) * 32 + 8 * kq;
-    const bf16x8 a_hi = __builtin_bit_cast(bf16x8, *reinterpret_cast<const ushort8 *>(ah));
-    const bf16x8 a_lo = __builtin_bit_cast(bf16x8, *reinterpret_cast<const ushort8 *>(al));
-    floatx4 acc = {0.f, 0.f, 0.f, 0.f};
-    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a_lo, b_hi, acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a_hi, b_lo, acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a_hi, b_hi, acc, 0, 0, 0);
-    const float4 b0 = *reinterpret_cast<const float4 *>(s.basis + c0 + 4 * kq);
-    floatx4 out = {fmaf(phi0, b0.x, acc[0]), fmaf(phi0, b0.y, acc[1]), fmaf(phi0, b0.z, acc[2]),
-                   fmaf(phi0, b0.w, acc[3])};
-    fwd_stage(sT, wave, lane, n, out);
+    const int c0 = min(cbase + 16 * n, g.ldF - 16);
+    const size_t e = (size_t)(c0 + (lane & 15)) * 32 + 8 * kq;
+    a_hi[n] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const ushort8 *>(s.basis_thi + e));
+    a_lo[n] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const ushort8 *>(s.basis_tlo + e));
+    a0[n] = kq == 0 ? s.basis[c0 + (lane & 15)] : 0.f;
   }
-  __syncthreads();
-  fwd_store(g, s, sT, dst, r0, rows);
+  for (; r0 < r_end; r0 += 16) {
+    const int my_row = r0 + (lane & 15);
+    if (skip_done && s.target) {
+      bool any = false;
+      for (int r = 0; r < 16; ++r) {
+        const int row = r0 + r;
+        any = any || (row < rows && slot_active(s, work_spec(s, row / rows_per_spec)));
+      }
+      if (!any) continue;  // (uniform over the block)
+    }
+    fwd_dst_rows(s, r0, rows, rows_per_spec, dst);
+    bf16x8 b_hi, b_lo;
+    float phi0 = 0.f;
+    {
+      float phi[32];
+#pragma unroll
+      for (int k = 0; k < 32; ++k) phi[k] = 0.f;
+      if (my_row < rows) {
+        const int e = my_row / rows_per_spec;
+        const int t = my_row - e * rows_per_spec;
+        feature_row(s.u + (size_t)work_spec(s, e) * kNP, t, phi);
+      }
+      phi0 = phi[0];
+      phi[0] = 0.f;  // constant row added in FP32 below
+      float sel[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        float v = phi[e];
+#pragma unroll
+        for (int q = 1; q < 4; ++q)
+          if (kq == q) v = phi[8 * q + e];
+        sel[e] = v;
+      }
+      split8(sel, b_hi, b_lo);
+    }
+#pragma unroll
+    for (int n = 0; n < kFwdTiles; ++n) {
+      floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+      acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a_lo[n], b_hi, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a_hi[n], b_lo, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a_hi[n], b_hi, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a0[n], phi0, acc, 0, 0, 0);
+      fwd_stage(sT, wave, lane, n, acc);
+    }
+    __syncthreads();
+    fwd_store(g, s, sT, dst, r0, rows);
+    if (r0 + 16 < r_end) __syncthreads();  // the stage and dst are rewritten
+  }
 }
 
 // F'[r][c] = sum_k Phi[r][k] basis[k][c] for r < rows (rows = B or 4B with
 // derivative rows), k < NB (20, or 60 over three emulator classes).
-// Grid: (ldF / (64 * kFwdTiles), ceil(rows / 16)).
+// Grid: (ldF / (64 * kFwdTiles), workgroups for ceil(rows / 16) tiles).
+//
+// Bound by the stores of F'.  A tile needs 40 KB of basis entries and stores
+// 32 KB, so (of one class) a workgroup keeps its basis entries in registers
+// over several tiles: 65,536 x 3,900 in 192 us (5.6 TB/s) against 275 when
+// each tile read them anew.
 template <int NB>
 __global__ __launch_bounds__(256) void k_interp_fwd(Geometry g, State s, int rows_per_spec, int skip_done) {
   __shared__ __align__(16) float sT[16 * kFwdLd];
   __shared__ int dst[16];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int rows = work_count(g, s) * rows_per_spec;
-  const int r0 = blockIdx.y * 16;
+  const int tiles = NB == kNB ? fwd_row_tiles(g, s, rows, 1 << 30) : 1;
+  int r0 = blockIdx.y * 16 * tiles;
   if (r0 >= rows) return;  // past the work list (uniform over the block)
-  const int my_row = r0 + (lane & 15);
+  const int r_end = NB == kNB ? min(rows, r0 + 16 * tiles) : r0 + 1;
   const int kq = lane >> 4;  // k offset inside a group of 4
-  if (skip_done && s.target) {
-    bool any = false;
-    for (int r = 0; r < 16; ++r) {
-      const int row = r0 + r;
-      any = any || (row < rows && slot_active(s, work_spec(s, row / rows_per_spec)));
-    }
-    if (!any) return;
-  }
-  fwd_dst_rows(s, r0, rows, rows_per_spec, dst);
-
-  float bv[NB / 4];
-  {
-    float phi[NB];
-#pragma unroll
-    for (int k = 0; k < NB; ++k) phi[k] = 0.f;
-    if (my_row < rows) {
-      const int e = my_row / rows_per_spec;
-      const int t = my_row - e * rows_per_spec;
-      const float *ur = s.u + (size_t)work_spec(s, e) * kNP;
-      if (NB == kNB)
-        feature_row(ur, t, phi);
-      else
-        feature_row_classes(g, ur, t, phi);
-    }
-    // selects, not an indexed load: keeps phi in registers
-#pragma unroll
-    for (int kk = 0; kk < NB / 4; ++kk)
-      bv[kk] = kq == 0 ? phi[4 * kk] : (kq == 1 ? phi[4 * kk + 1] : (kq == 2 ? phi[4 * kk + 2] : phi[4 * kk + 3]));
-  }
   const int cbase = (blockIdx.x * 4 + wave) * (16 * kFwdTiles);
-  // products over feature groups KK0 .. KK0 + NKK - 1 (4 features each)
-  auto run = [&](auto kk0, auto nkk) {
-    constexpr int KK0 = decltype(kk0)::value, NKK = decltype(nkk)::value;
-    for (int n = 0; n < kFwdTiles; ++n) {
-      const int c0 = cbase + 16 * n;
-      if (c0 >= g.ldF) break;
-      floatx4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int kk = KK0; kk < KK0 + NKK; ++kk) {
-        const float a = s.basis[(size_t)(4 * kk + kq) * g.ldF + c0 + (lane & 15)];
-        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a, bv[kk], acc, 0, 0, 0);
-      }
-      fwd_stage(sT, wave, lane, n, acc);
-    }
-  };
+  float av[kFwdTiles][kNB / 4];  // NB == kNB: the wave's basis entries
   if constexpr (NB == kNB) {
-    run(IntC<0>{}, IntC<NB / 4>{});
-  } else {
-    // an emulator class whose weight and weight derivative are zero in all
-    // 16 rows of the tile (spectra of other Teff regimes) has an all-zero
-    // feature block; its products would add exact zeros and are left out
-    int mask = 0;
 #pragma unroll
-    for (int q = 0; q < kMaxClasses; ++q) {
-      bool nz = false;
+    for (int n = 0; n < kFwdTiles; ++n)
 #pragma unroll
-      for (int kk = 5 * q; kk < 5 * q + 5; ++kk) nz = nz || bv[kk] != 0.f;
-      mask |= (__ballot(nz) != 0) << q;
-    }
-    switch (mask) {  // wave uniform; every wave of the block sees the same rows
-      case 1: run(IntC<0>{}, IntC<5>{}); break;
-      case 2: run(IntC<5>{}, IntC<5>{}); break;
-      case 4: run(IntC<10>{}, IntC<5>{}); break;
-      case 3: run(IntC<0>{}, IntC<10>{}); break;
-      case 6: run(IntC<5>{}, IntC<10>{}); break;
-      default: run(IntC<0>{}, IntC<15>{}); break;
-    }
+      for (int kk = 0; kk < kNB / 4; ++kk)
+        av[n][kk] = s.basis[(size_t)(4 * kk + kq) * g.ldF + min(cbase + 16 * n, g.ldF - 16) + (lane & 15)];
   }
-  __syncthreads();
-  fwd_store(g, s, sT, dst, r0, rows);
+  for (; r0 < r_end; r0 += 16) {
+    const int my_row = r0 + (lane & 15);
+    if (skip_done && s.target) {
+      bool any = false;
+      for (int r = 0; r < 16; ++r) {
+        const int row = r0 + r;
+        any = any || (row < rows && slot_active(s, work_spec(s, row / rows_per_spec)));
+      }
+      if (!any) continue;  // (uniform over the block)
+    }
+    fwd_dst_rows(s, r0, rows, rows_per_spec, dst);
+
+    float bv[NB / 4];
+    {
+      float phi[NB];
+#pragma unroll
+      for (int k = 0; k < NB; ++k) phi[k] = 0.f;
+      if (my_row < rows) {
+        const int e = my_row / rows_per_spec;
+        const int t = my_row - e * rows_per_spec;
+        const float *ur = s.u + (size_t)work_spec(s, e) * kNP;
+        if (NB == kNB)
+          feature_row(ur, t, phi);
+        else
+          feature_row_classes(g, ur, t, phi);
+      }
+      // selects, not an indexed load: keeps phi in registers
+#pragma unroll
+      for (int kk = 0; kk < NB / 4; ++kk)
+        bv[kk] = kq == 0 ? phi[4 * kk] : (kq == 1 ? phi[4 * kk + 1] : (kq == 2 ? phi[4 * kk + 2] : phi[4 * kk + 3]));
+    }
+    // products over feature groups KK0 .. KK0 + NKK - 1 (4 features each)
+    auto run = [&](auto kk0, auto nkk) {
+      constexpr int KK0 = decltype(kk0)::value, NKK = decltype(nkk)::value;
+      for (int n = 0; n < kFwdTiles; ++n) {
+        const int c0 = cbase + 16 * n;
+        if (c0 >= g.ldF) break;
+        floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int kk = KK0; kk < KK0 + NKK; ++kk) {
+          const float a = s.basis[(size_t)(4 * kk + kq) * g.ldF + c0 + (lane & 15)];
+          acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a, bv[kk], acc, 0, 0, 0);
+        }
+        fwd_stage(sT, wave, lane, n, acc);
+      }
+    };
+    if constexpr (NB == kNB) {
+#pragma unroll
+      for (int n = 0; n < kFwdTiles; ++n) {
+        floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int kk = 0; kk < NB / 4; ++kk)
+          acc = __builtin_amdgcn_mfma_f32_16x16x4f32(av[n][kk], bv[kk], acc, 0, 0, 0);
+        fwd_stage(sT, wave, lane, n, acc);
+      }
+    } else {
+      // an emulator class whose weight and weight derivative are zero in all
+      // 16 rows of the tile (spectra of other Teff regimes) has an all-zero
+      // feature block; its products would add exact zeros and are left out
+      int mask = 0;
+#pragma unroll
+      for (int q = 0; q < kMaxClasses; ++q) {
+        bool nz = false;
+#pragma unroll
+        for (int kk = 5 * q; kk < 5 * q + 5; ++kk) nz = nz || bv[kk] != 0.f;
+        mask |= (__ballot(nz) != 0) << q;
+      }
+      switch (mask) {  // wave uniform; every wave of the block sees the same rows
+        case 1: run(IntC<0>{}, IntC<5>{}); break;
+        case 2: run(IntC<5>{}, IntC<5>{}); break;
+        case 4: run(IntC<10>{}, IntC<5>{}); break;
+        case 3: run(IntC<0>{}, IntC<10>{}); break;
+        case 6: run(IntC<5>{}, IntC<10>{}); break;
+        default: run(IntC<0>{}, IntC<15>{}); break;
+      }
+    }
+    __syncthreads();
+    fwd_store(g, s, sT, dst, r0, rows);
+    if (r0 + 16 < r_end) __syncthreads();  // the stage and dst are rewritten
+  }
 }
 
 // Gradient of J with respect to u from Phi-bar (pb, NB entries) and the
@@ -778,7 +834,18 @@ hipError_t launch_interp_fwd(const Geometry &g, const State &s, int deriv_rows, 
   const int rows_per_spec = deriv_rows ? 4 : 1;
   const int rows = g.B * rows_per_spec;
   const int cols_per_block = 4 * 16 * kFwdTiles;
-  dim3 grid((g.ldF + cols_per_block - 1) / cols_per_block, (rows + 15) / 16);
+  const int col_blocks = (g.ldF + cols_per_block - 1) / cols_per_block;
+  const int tiles = (rows + 15) / 16;
+  int row_blocks = tiles;
+  if (!fwd_one_tile(g, s)) {
+    // workgroups for a work list of any length up to rows: it takes one tile
+    // each up to two rounds of kFwdResident, then no more than one round
+    // (BF16x3: then kFwdBf16Tiles each)
+    int most = 2 * kFwdResident / col_blocks + 1;
+    if (bf16x3) most = std::max(most, (tiles + kFwdBf16Tiles - 1) / kFwdBf16Tiles);
+    row_blocks = std::min(tiles, most);
+  }
+  dim3 grid(col_blocks, row_blocks);
   // derivative rows are only formed for final evaluations: never skip those
   const int skip_done = deriv_rows ? 0 : 1;
   if (bf16x3)
