@@ -31,45 +31,53 @@ struct IntC {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef unsigned short ushort8 __attribute__((ext_vector_type(8)));
 
-// Round to nearest even (finite inputs).
-__device__ inline uint16_t f2bf(float f) {
-  uint32_t u = __float_as_uint(f);
-  u += 0x7FFFu + ((u >> 16) & 1u);
-  return (uint16_t)(u >> 16);
-}
-__device__ inline float bf2f(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
-
+// x = hi + lo in bf16, rounded to nearest even (finite inputs).
 __device__ inline void split8(const float *x, bf16x8 &hi, bf16x8 &lo) {
-  ushort8 h, l;
 #pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    const uint16_t a = f2bf(x[e]);
-    h[e] = a;
-    l[e] = f2bf(x[e] - bf2f(a));
-  }
-  hi = __builtin_bit_cast(bf16x8, h);
-  lo = __builtin_bit_cast(bf16x8, l);
+  for (int e = 0; e < 8; ++e) hi[e] = (__bf16)x[e];
+  const ushort8 h = __builtin_bit_cast(ushort8, hi);
+#pragma unroll
+  for (int e = 0; e < 8; ++e) lo[e] = (__bf16)(x[e] - __uint_as_float((uint32_t)h[e] << 16));
 }
 
-// hi/lo copies of the padded basis: [20][ldF] for the adjoint contraction and
-// [ldF][32] (k-major, rows 1..19, zeros elsewhere) for the forward one.
-__global__ void k_split_basis(Geometry g, State s) {
-  const int c = blockIdx.x * blockDim.x + threadIdx.x;
-  if (c >= g.ldF) return;
-#pragma unroll 1
-  for (int k = 0; k < 32; ++k) {
-    uint16_t hi = 0, lo = 0;
-    if (k < kNB) {
-      const float x = s.basis[(size_t)k * g.ldF + c];
-      hi = f2bf(x);
-      lo = f2bf(x - bf2f(hi));
-      s.basis_hi[(size_t)k * g.ldF + c] = hi;
-      s.basis_lo[(size_t)k * g.ldF + c] = lo;
+// hi/lo copies of the padded basis in the products' operand order, 16 bytes a
+// lane and a wave's load contiguous.  Adjoint contraction: of each 32 columns,
+// rows 0-15 by lane (row + 16 kq: columns 8 kq .. + 7), then of all, rows 16-19
+// by row - 16 + 4 kq.  Forward: of each 16 columns, lane (column + 16 kq) holds
+// rows 8 kq .. + 7 (rows 1..19, zeros elsewhere).  Grid: (ldF / 256, 20 rows +
+// 4 quarters): 5 us for 4,096 columns, 15 with one thread for all of a column.
+__global__ __launch_bounds__(256) void k_split_basis(Geometry g, State s) {
+  const int j = blockIdx.x * 256 + threadIdx.x;
+  float x[8];
+  ushort8 *hi, *lo;
+  if (blockIdx.y < kNB) {
+    const int k = blockIdx.y;
+    if (j >= g.ldF / 8) return;
+    const float4 *p = reinterpret_cast<const float4 *>(s.basis + (size_t)k * g.ldF) + 2 * j;
+    const float4 x0 = p[0], x1 = p[1];
+    x[0] = x0.x; x[1] = x0.y; x[2] = x0.z; x[3] = x0.w;
+    x[4] = x1.x; x[5] = x1.y; x[6] = x1.z; x[7] = x1.w;
+    const int chunk = j >> 2, kq = j & 3;
+    const size_t at = k < 16 ? (size_t)chunk * 64 + 16 * kq + k
+                             : (size_t)2 * g.ldF + (size_t)chunk * 16 + 4 * kq + (k - 16);
+    hi = reinterpret_cast<ushort8 *>(s.basis_hi) + at;
+    lo = reinterpret_cast<ushort8 *>(s.basis_lo) + at;
+  } else {
+    const int kq = blockIdx.y - kNB;
+    if (j >= g.ldF) return;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const int k = 8 * kq + e;
+      x[e] = k >= 1 && k < kNB ? s.basis[(size_t)k * g.ldF + j] : 0.f;
     }
-    const bool fwd = k >= 1 && k < kNB;
-    s.basis_thi[(size_t)c * 32 + k] = fwd ? hi : 0;
-    s.basis_tlo[(size_t)c * 32 + k] = fwd ? lo : 0;
+    const size_t at = (size_t)(j >> 4) * 64 + 16 * kq + (j & 15);
+    hi = reinterpret_cast<ushort8 *>(s.basis_thi) + at;
+    lo = reinterpret_cast<ushort8 *>(s.basis_tlo) + at;
   }
+  bf16x8 h, l;
+  split8(x, h, l);
+  *hi = __builtin_bit_cast(ushort8, h);
+  *lo = __builtin_bit_cast(ushort8, l);
 }
 
 // Output staging of the forward contraction: a workgroup's 16 rows x 512
@@ -153,9 +161,9 @@ __global__ __launch_bounds__(256) void k_interp_fwd_bf16(Geometry g, State s, in
 #pragma unroll
   for (int n = 0; n < kFwdTiles; ++n) {
     const int c0 = min(cbase + 16 * n, g.ldF - 16);
-    const size_t e = (size_t)(c0 + (lane & 15)) * 32 + 8 * kq;
-    a_hi[n] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const ushort8 *>(s.basis_thi + e));
-    a_lo[n] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const ushort8 *>(s.basis_tlo + e));
+    const size_t e = (size_t)c0 * 4 + lane;
+    a_hi[n] = __builtin_bit_cast(bf16x8, reinterpret_cast<const ushort8 *>(s.basis_thi)[e]);
+    a_lo[n] = __builtin_bit_cast(bf16x8, reinterpret_cast<const ushort8 *>(s.basis_tlo)[e]);
     a0[n] = kq == 0 ? s.basis[c0 + (lane & 15)] : 0.f;
   }
   for (; r0 < r_end; r0 += 16) {
@@ -409,11 +417,15 @@ __device__ inline void bwd_epilogue(const Geometry &g, const State &s, const Ada
 
 // BF16x3 variant of the adjoint contraction (one emulator class): one
 // workgroup = 16 spectra; its four waves split the columns and combine
-// through LDS.
+// through LDS.  Bound by the loads of F-bar' and their latency (two 1 KB loads
+// a wave in flight; three chunks ahead gained nothing): 16,384 x 3,900 in 74 us
+// (3.6 TB/s), 91 when F-bar' and the basis rows were read with a row per lane.
 __global__ __launch_bounds__(256) void k_interp_bwd_bf16(Geometry g, State s, AdamCfg adam,
                                                          int do_adam, float *grad_out) {
   constexpr int NB = kNB;
   constexpr int NG = 2;
+  constexpr int kLd = 36;  // row stride of a wave's [16][32] stage
+  __shared__ __align__(16) float stage[4][16 * kLd];
   __shared__ float red[4][16][16 * NG];
   __shared__ float pb[16][NB];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -422,15 +434,6 @@ __global__ __launch_bounds__(256) void k_interp_bwd_bf16(Geometry g, State s, Ad
   if (s0 >= count) return;  // past the work list (uniform over the block)
   const int i_row = lane & 15;   // spectrum within the tile (A rows) / basis row (B cols)
   const int kq = lane >> 4;
-  const bool row_ok = s0 + i_row < count;
-  const float *fb_row = s.fbar + (size_t)work_spec(s, row_ok ? s0 + i_row : s0) * g.ldF;
-  bool b_ok[NG];
-  int b_row[NG];
-#pragma unroll
-  for (int q = 0; q < NG; ++q) {
-    b_ok[q] = 16 * q + i_row < NB;
-    b_row[q] = 16 * q + (b_ok[q] ? i_row : 0);
-  }
   if (s.target) {  // the whole tile finished: nothing to do (uniform over the block)
     bool any = false;
     for (int r = 0; r < 16; ++r) any = any || (s0 + r < count && slot_active(s, work_spec(s, s0 + r)));
@@ -443,31 +446,54 @@ __global__ __launch_bounds__(256) void k_interp_bwd_bf16(Geometry g, State s, Ad
   const int per_wave = g.ldF / 4;  // ldF is a multiple of 128
   const int cb = wave * per_wave;
   const int ce = cb + per_wave;
-  const uint16_t *h0 = s.basis_hi + (size_t)b_row[0] * g.ldF;
-  const uint16_t *l0 = s.basis_lo + (size_t)b_row[0] * g.ldF;
-  const uint16_t *h1 = s.basis_hi + (size_t)b_row[1] * g.ldF;
-  const uint16_t *l1 = s.basis_lo + (size_t)b_row[1] * g.ldF;
+  const ushort8 *h0 = reinterpret_cast<const ushort8 *>(s.basis_hi) + lane;
+  const ushort8 *l0 = reinterpret_cast<const ushort8 *>(s.basis_lo) + lane;
+  const bool b_ok = i_row < NB - 16;  // the lanes of basis rows 16-19
+  const size_t at1 = (size_t)2 * g.ldF + 4 * kq + (b_ok ? i_row : 0);
+  const ushort8 *h1 = reinterpret_cast<const ushort8 *>(s.basis_hi) + at1;
+  const ushort8 *l1 = reinterpret_cast<const ushort8 *>(s.basis_lo) + at1;
   const bf16x8 zero = __builtin_bit_cast(bf16x8, ushort8{0, 0, 0, 0, 0, 0, 0, 0});
-  for (int c = cb; c < ce; c += 32) {
-    const int cc = c + 8 * kq;
-    float fa[8];
-    if (row_ok) {
-      const float4 x0 = *reinterpret_cast<const float4 *>(fb_row + cc);
-      const float4 x1 = *reinterpret_cast<const float4 *>(fb_row + cc + 4);
-      fa[0] = x0.x; fa[1] = x0.y; fa[2] = x0.z; fa[3] = x0.w;
-      fa[4] = x1.x; fa[5] = x1.y; fa[6] = x1.z; fa[7] = x1.w;
-    } else {
+  // F-bar' passes through LDS: eight lanes read 128 bytes of a row (read with
+  // a row per lane, a load touches 16 cache lines with each quarter of the
+  // wave), the next 32 columns while these are at work.
+  float *stg = stage[wave];
+  const int sr = lane >> 3, sc = 4 * (lane & 7);
+  const float *rp[2];
+  bool rv[2];
 #pragma unroll
-      for (int e = 0; e < 8; ++e) fa[e] = 0.f;
-    }
+  for (int j = 0; j < 2; ++j) {
+    rv[j] = s0 + 8 * j + sr < count;
+    rp[j] = s.fbar + (size_t)work_spec(s, rv[j] ? s0 + 8 * j + sr : s0) * g.ldF + sc;
+  }
+  float4 fv[2];
+  auto fetch = [&](int c) {
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+      fv[j] = rv[j] ? *reinterpret_cast<const float4 *>(rp[j] + c) : make_float4(0.f, 0.f, 0.f, 0.f);
+  };
+  fetch(cb);
+  for (int c = cb; c < ce; c += 32) {
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+      *reinterpret_cast<float4 *>(stg + (8 * j + sr) * kLd + sc) = fv[j];
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    if (c + 32 < ce) fetch(c + 32);
+    const float4 x0 = *reinterpret_cast<const float4 *>(stg + i_row * kLd + 8 * kq);
+    const float4 x1 = *reinterpret_cast<const float4 *>(stg + i_row * kLd + 8 * kq + 4);
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    const float fa[8] = {x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w};
     bf16x8 a_hi, a_lo;
     split8(fa, a_hi, a_lo);
-    const bf16x8 bh0 = __builtin_bit_cast(bf16x8, *reinterpret_cast<const ushort8 *>(h0 + cc));
-    const bf16x8 bl0 = __builtin_bit_cast(bf16x8, *reinterpret_cast<const ushort8 *>(l0 + cc));
+    const bf16x8 bh0 = __builtin_bit_cast(bf16x8, h0[2 * c]);
+    const bf16x8 bl0 = __builtin_bit_cast(bf16x8, l0[2 * c]);
     bf16x8 bh1 = zero, bl1 = zero;
-    if (b_ok[1]) {
-      bh1 = __builtin_bit_cast(bf16x8, *reinterpret_cast<const ushort8 *>(h1 + cc));
-      bl1 = __builtin_bit_cast(bf16x8, *reinterpret_cast<const ushort8 *>(l1 + cc));
+    if (b_ok) {
+      bh1 = __builtin_bit_cast(bf16x8, h1[c / 2]);
+      bl1 = __builtin_bit_cast(bf16x8, l1[c / 2]);
     }
     acc[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a_lo, bh0, acc[0], 0, 0, 0);
     acc[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a_lo, bh1, acc[1], 0, 0, 0);
@@ -874,7 +900,7 @@ hipError_t launch_interp_bwd(const Geometry &g, const State &s, const AdamCfg *a
 }
 
 hipError_t launch_split_basis(const Geometry &g, const State &s, hipStream_t st) {
-  hipLaunchKernelGGL(k_split_basis, dim3((g.ldF + 255) / 256), dim3(256), 0, st, g, s);
+  hipLaunchKernelGGL(k_split_basis, dim3((g.ldF + 255) / 256, kNB + 4), dim3(256), 0, st, g, s);
   return hipGetLastError();
 }
 

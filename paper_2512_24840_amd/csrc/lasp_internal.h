@@ -90,10 +90,10 @@ struct State {
   const int *order;     // [B] spectrum indices, active ones first
   const int *n_active;  // [1] length of the list
   float *basis;     // [nb][ldF] zero-padded copy of the basis
-  uint16_t *basis_hi;  // [20][ldF] bf16 high part (BF16x3, adjoint contraction)
-  uint16_t *basis_lo;  // [20][ldF] bf16 low part
-  uint16_t *basis_thi; // [ldF][32] bf16 high part, k-major per column, rows 1..19 (forward)
-  uint16_t *basis_tlo; // [ldF][32] bf16 low part
+  uint16_t *basis_hi;  // 20 x ldF, bf16 high part in operand order (BF16x3, adjoint contraction)
+  uint16_t *basis_lo;  // 20 x ldF, bf16 low part
+  uint16_t *basis_thi; // 32 x ldF, bf16 high part in operand order, rows 1..19 (forward)
+  uint16_t *basis_tlo; // 32 x ldF, bf16 low part
 };
 
 // Inputs and outputs of the Clean mask kernel.  obs, ivar and model are
