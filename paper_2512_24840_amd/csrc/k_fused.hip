@@ -118,11 +118,9 @@ __host__ __device__ inline FusedLayout fused_layout(const Geometry &g, int nwave
 // the result.
 //
 // Four waves per SIMD: the register budget is held to 128 per lane, so with
-// the LDS above four 256-thread or two 512-thread workgroups share a CU.  The
-// price is a few spills: at 3,900 pixels 40 bytes per lane (some of the
-// lane's (o/w, W w^2) pairs, parked in scratch between the moments and the
-// residual: one store and one load each per pass); measured faster than
-// three waves per SIMD without spills, for both pixel counts.
+// the LDS above four 256-thread or two 512-thread workgroups share a CU.  No
+// spills with one arm at 3,900 pixels, 52 bytes per lane with several arms;
+// measured faster than three waves per SIMD, for both pixel counts.
 //
 // ONESHOT: the pass of an evaluation at given parameters (lasp_forward).  It
 // prepares its spectrum itself: the row goes from obs and ivar through LDS

@@ -20,7 +20,8 @@ DEV = torch.device("cuda:0")
     ("lamost3900", 32, 1, 4, 5, 7), ("lamost3900", 257, 17, 4, 5, 7),
     ("lamost1550", 1550, 64, 8, 5, 30), ("lamost3900", 2048, 64, 6, 5, 1),
     ("lamost3900", 2176, 64, 6, 5, 7), ("lamost3900", 2177, 64, 6, 5, 7),
-    ("lamost3900", 3900, 64, 10, 5, 30), ("lamost3900", 4352, 64, 10, 5, 7),
+    ("lamost3900", 3900, 64, 10, 5, 30), ("lamost3900", 4224, 64, 10, 5, 7),
+    ("lamost3900", 4225, 64, 10, 5, 7), ("lamost3900", 4352, 64, 10, 5, 7),
     ("lamost3900", 4353, 64, 10, 5, 7), ("desi7800", 7800, 64, 10, 5, 7),
     ("desi7800", 8576, 64, 10, 5, 7), ("lamost3900", 257, 17, 4, 1024, 3),
     ("lamost3900", 257, 17, 4, 1025, 26), ("lamost3900", 4353, 64, 4, 256, 3),
