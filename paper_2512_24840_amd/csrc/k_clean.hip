@@ -17,6 +17,8 @@
 // (o/w, W w^2) array.
 #include "lasp_internal.h"
 
+#include <type_traits>
+
 namespace lasp {
 namespace {
 
@@ -26,8 +28,12 @@ constexpr int kMaxDPasses = 20;
 // access to memory is coalesced (a lane's own 17 pixels would put the 64
 // lanes of each access on 64 cache lines), and a pixel keeps two values in
 // registers: its residual and the excess |eps| - f G that all tests use.
-// Measured at 16,384 x 3,900 (0.83 GB): 0.249 ms, against 0.566 ms with
-// lane-strided accesses and three values per pixel.
+// Bound half by the rows' latency and half by VALU issue (FP64 tests), so the
+// three rows' loads fly together, each |m_j - m_{j+1}| is formed once and the
+// sum over all valid pixels takes no tests.  Measured at 16,384 x 3,900 (0.83
+// GB), a call: 0.217 ms (3.8 TB/s), 0.232 with the rows one after another and
+// each difference twice, 0.546 with lane-strided accesses and three values per
+// pixel.
 template <int BLOCK>
 __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(4))) void k_clean(
     Geometry g, CleanArgs a) {
@@ -47,12 +53,16 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(4))) void
   const int j0 = tid * kNPL;
   const size_t row = (size_t)spec * P;
 
-  // one row through LDS: the lane's pixels and the two beside them
-  auto fetch = [&](const float *src, float (&v)[kNPL + 2]) {
-    float x[kNPL];
+  // the rows' loads fly together, then each row goes through LDS: the lane's
+  // pixels and the two beside them
+  float xm[kNPL], xo[kNPL], xi[kNPL];
 #pragma unroll
-    for (int i = 0; i < kNPL; ++i) x[i] = src[row + min(tid + i * BLOCK, P - 1)];
-    __syncthreads();  // the previous row has been read
+  for (int i = 0; i < kNPL; ++i) xm[i] = a.model[row + min(tid + i * BLOCK, P - 1)];
+#pragma unroll
+  for (int i = 0; i < kNPL; ++i) xo[i] = a.obs[row + min(tid + i * BLOCK, P - 1)];
+#pragma unroll
+  for (int i = 0; i < kNPL; ++i) xi[i] = a.ivar[row + min(tid + i * BLOCK, P - 1)];
+  auto turn = [&](const float (&x)[kNPL], float (&v)[kNPL + 2]) {
 #pragma unroll
     for (int i = 0; i < kNPL; ++i) sRow[tid + i * BLOCK] = x[i];
     __syncthreads();
@@ -60,15 +70,17 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(4))) void
     for (int i = 0; i < kNPL; ++i) v[i + 1] = sRow[j0 + i];
     v[0] = sRow[max(j0 - 1, 0)];
     v[kNPL + 1] = sRow[min(j0 + kNPL, kRow - 1)];
+    __syncthreads();  // read before the next row comes
   };
   float m[kNPL + 2], o[kNPL + 2], iv[kNPL + 2];
-  fetch(a.model, m);
-  fetch(a.obs, o);
-  fetch(a.ivar, iv);
+  turn(xm, m);
+  turn(xo, o);
+  turn(xi, iv);
   double eps[kNPL], exc[kNPL];  // residual (0 where invalid), |residual| - f G
   double el = 0.0, er = 0.0;    // residuals of pixels j0 - 1 and j0 + 17
   uint32_t valid = 0;
   const double f = (double)a.f_shift;
+  double gl = j0 > 0 ? fabs((double)m[1] - (double)m[0]) : 0.0;
 #pragma unroll
   for (int i = -1; i <= kNPL; ++i) {
     const int j = j0 + i;
@@ -83,10 +95,9 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(4))) void
       if (ok) valid |= 1u << i;
       eps[i] = e;
       // flux gradient G_j = max(|m_j - m_{j-1}|, |m_j - m_{j+1}|), ends use one side
-      const double mj = (double)m[i + 1];
-      const double gl = j > 0 ? fabs(mj - (double)m[i]) : 0.0;
-      const double gr = j + 1 < P ? fabs(mj - (double)m[i + 2]) : 0.0;
+      const double gr = j + 1 < P ? fabs((double)m[i + 1] - (double)m[i + 2]) : 0.0;
       exc[i] = fma(-f, fmax(gl, gr), fabs(e));
+      gl = gr;
     }
   }
 
@@ -101,12 +112,13 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(4))) void
     for (int w = 0; w < NW; ++w) t += sCnt[slot][w];
     return t;
   };
-  // sample standard deviation of eps over the selected pixels
-  auto stats = [&](uint32_t sel, int n) {
+  // sample standard deviation of eps over the selected pixels (all: the valid
+  // ones; the others' residuals are zero)
+  auto stats = [&](auto all, uint32_t sel, int n) {
     double acc[1] = {0.0};
 #pragma unroll
     for (int i = 0; i < kNPL; ++i)
-      if (sel >> i & 1u) acc[0] += eps[i];
+      if (all.value || (sel >> i & 1u)) acc[0] += eps[i];
     block_sum_lds<NW, 1>(acc, sScr, sRed, sOut, lane, wave);
     const double mean = n > 0 ? sOut[0] / (double)n : 0.0;
     double v[1] = {0.0};
@@ -117,7 +129,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(4))) void
     return n > 1 ? sqrt(sOut[1] / ((double)n - 1.0)) : 0.0;
   };
   const int nv = count(valid);  // its barrier also ends the last row's reads
-  const double sigma = stats(valid, nv);
+  const double sigma = stats(std::true_type{}, valid, nv);
 
   // B with the relaxed thresholds k = 3, 4, 5, 7 (the last one stands if
   // every count is above 3 %)
@@ -151,7 +163,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(4))) void
       if ((valid & near) >> i & 1u && exc[i] > 2.0 * sigma) cout |= 1u << i;
   }
   const uint32_t kept = valid & ~bout & ~cout;
-  const double sigma2 = stats(kept, count(kept));
+  const double sigma2 = stats(std::false_type{}, kept, count(kept));
 
   // D: grow from the outliers through same-sign, not larger neighbours; the
   // pixels that may join, by which side
