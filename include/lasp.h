@@ -233,7 +233,8 @@ int lasp_fit_group(const float *obs, const float *ivar, const double *wave_grid,
  *   out_jac   [B][5][P] float d model / d u at fixed continuum, or NULL
  *   out_cov   [B][5][5] double covariance at u in physical units
  *             (Section 2.2 stage 9), or NULL
- * Other arguments as in lasp_fit_group (opts->out_chi2 is ignored).
+ * Other arguments as in lasp_fit_group (opts->out_chi2 is ignored).  An output
+ * may lie in the memory of obs, ivar, basis or u: all of them are read first.
  */
 int lasp_forward(const float *obs, const float *ivar, const double *wave_grid,
                  const float *basis, const float *u, float *out_model, double *out_chi2,

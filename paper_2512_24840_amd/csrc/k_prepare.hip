@@ -158,6 +158,23 @@ __global__ void k_progress(Geometry g, State s, int32_t *steps, int32_t *done) {
   if (done) done[spec] = (s.target && t >= s.target[spec]) ? 1 : 0;
 }
 
+// Per-spectrum results of a forward evaluation whose outputs lie in the memory
+// of its inputs or of one another: chi2, the objective J = chi2 / n_eff of
+// Eq. 9 (read per spectrum), n_eff and status (with OUT_OF_BOX of the
+// evaluated u), out of the scratch after the last kernel.
+__global__ void k_outputs(Geometry g, State s, double *chi2_out, float *J_out, int32_t *neff_out,
+                          uint32_t *status_out) {
+  const int spec = blockIdx.x * blockDim.x + threadIdx.x;
+  if (spec >= g.B) return;
+  const double c = s.chi2[spec];
+  const int n = s.neff[spec];
+  const uint32_t st = (s.status[spec] & ~kStOutOfBox) | box_bit(s.u + (size_t)spec * kNP);
+  if (chi2_out) chi2_out[spec] = c;
+  if (J_out) J_out[spec] = n > 0 ? (float)(c / (double)n) : 0.f;
+  if (neff_out) neff_out[spec] = n;
+  if (status_out) status_out[spec] = st;
+}
+
 }  // namespace
 
 hipError_t launch_prepare(const Geometry &g, const State &s, const float *obs, const float *ivar,
@@ -198,6 +215,14 @@ hipError_t launch_progress(const Geometry &g, const State &s, int32_t *steps, in
                            hipStream_t st) {
   const int bs = 256;
   hipLaunchKernelGGL(k_progress, dim3((g.B + bs - 1) / bs), dim3(bs), 0, st, g, s, steps, done);
+  return hipGetLastError();
+}
+
+hipError_t launch_outputs(const Geometry &g, const State &s, double *chi2_out, float *J_out,
+                          int32_t *neff_out, uint32_t *status_out, hipStream_t st) {
+  const int bs = 256;
+  hipLaunchKernelGGL(k_outputs, dim3((g.B + bs - 1) / bs), dim3(bs), 0, st, g, s, chi2_out, J_out,
+                     neff_out, status_out);
   return hipGetLastError();
 }
 

@@ -434,10 +434,20 @@ lasp::CovArgs cov_args(const lasp_opts *o) {
   return ca;
 }
 
+struct Range {
+  const char *beg, *end;  // empty: not there
+  Range(const void *p, size_t bytes) : beg((const char *)p), end(p ? beg + bytes : beg) {}
+  bool meets(const Range &o) const { return beg < o.end && o.beg < end; }
+};
+
 // Launch sequence of a forward evaluation at fixed u on the buffers of s
 // (fp rows: 4 when the Jacobian or covariance is wanted, else 1).  The
-// kernels read u and write chi2, n_eff and the status where the caller wants
-// them; nothing is copied.
+// one-shot passes read u and a spectrum's row of obs and ivar, and write chi2,
+// n_eff and the status where the caller wants them, workgroup by workgroup:
+// nothing is copied.  Outputs that lie in the memory of obs or ivar, or of one
+// another, would be written while other workgroups still read there; the rows
+// of such a call are prepared first, and what its kernels read back stays in
+// the scratch until the last of them has run.
 int forward_enqueue(const Geometry &g, State s, const float *obs, const float *ivar,
                     const float *basis, const float *u, float *out_model, double *out_chi2,
                     float *out_J, int32_t *out_neff, float *out_grad, float *out_jac,
@@ -446,22 +456,34 @@ int forward_enqueue(const Geometry &g, State s, const float *obs, const float *i
   const bool rows4 = out_jac || out_cov;
   s.target = nullptr;
   const size_t B = (size_t)g.B, P = (size_t)g.P, u_bytes = B * lasp::kNP * sizeof(float);
-  auto over_u = [&](const void *p, size_t bytes) {
-    const char *a = (const char *)p, *b = (const char *)u;
-    return p && a < b + u_bytes && b < a + bytes;
-  };
-  if (over_u(out_model, 4 * B * P) || over_u(out_chi2, 8 * B) || over_u(out_J, 4 * B) ||
-      over_u(out_neff, 4 * B) || over_u(out_grad, u_bytes) || over_u(out_jac, 20 * B * P) ||
-      over_u(out_cov, 200 * B) || over_u(opts->status, 4 * B))  // an output takes u's place
+  const Range in_obs(obs, 4 * B * P), in_ivar(ivar, 4 * B * P), in_u(u, u_bytes);
+  const Range outs[] = {{out_model, 4 * B * P}, {out_chi2, 8 * B},      {out_J, 4 * B},
+                        {out_neff, 4 * B},      {out_grad, u_bytes},    {out_jac, 20 * B * P},
+                        {out_cov, 200 * B},     {opts->status, 4 * B}};
+  bool over_u = false, apart = true;
+  for (const Range &a : outs) {
+    over_u = over_u || a.meets(in_u);
+    apart = apart && !a.meets(in_obs) && !a.meets(in_ivar);
+    for (const Range *b = outs; b != &a; ++b) apart = apart && !a.meets(*b);
+  }
+  if (over_u)  // an output takes u's place
     LASP_CHECK(hipMemcpyAsync(s.u, u, u_bytes, hipMemcpyDeviceToDevice, st), "copy u");
   else
     s.u = const_cast<float *>(u);  // no kernel below takes a step
-  s.chi2 = out_chi2;
-  if (out_neff) s.neff = out_neff;
-  if (opts->status) s.status = opts->status;
+  if (apart) {
+    s.chi2 = out_chi2;
+    if (out_neff) s.neff = out_neff;
+    if (opts->status) s.status = opts->status;
+  }
   const int bf16 = opts->precision == LASP_PREC_BF16X3;
   int rc = copy_basis(g, s, basis, bf16, st);
   if (rc) return rc;
+  if (!apart) {
+    LASP_TIMED(LASP_K_PREPARE, st);
+    LASP_CHECK(lasp::launch_prepare(g, s, obs, ivar, nullptr, opts->box_lo, opts->box_hi,
+                                    opts->weight_quantile, 0, 0, st),
+               "prepare");
+  }
   s.fp_stride = rows4 ? 4 * g.ldF : g.ldF;
   {
     LASP_TIMED(LASP_K_INTERP_FWD, st);
@@ -471,7 +493,13 @@ int forward_enqueue(const Geometry &g, State s, const float *obs, const float *i
   if (!rows4 || out_grad) {
     LASP_TIMED(LASP_K_FUSED, st);
     os.write_ow = rows4 ? 1 : 0;
-    LASP_CHECK(lasp::launch_fused_oneshot(g, s, out_grad ? 1 : 0, out_model, os, st), "fused pass");
+    if (apart) {
+      LASP_CHECK(lasp::launch_fused_oneshot(g, s, out_grad ? 1 : 0, out_model, os, st),
+                 "fused pass");
+    } else {  // a prepared adjoint pass writes neither model nor status
+      LASP_CHECK(lasp::launch_fused(g, s, 0, out_model, 1, st), "fused pass");
+      if (out_grad) LASP_CHECK(lasp::launch_fused(g, s, 1, nullptr, 0, st), "fused pass");
+    }
   }
   if (out_grad) {
     LASP_TIMED(LASP_K_INTERP_BWD, st);
@@ -482,15 +510,17 @@ int forward_enqueue(const Geometry &g, State s, const float *obs, const float *i
     lasp::CovArgs ca = cov_args(opts);
     ca.out_jac = out_jac;
     ca.out_cov = out_cov;
-    if (out_grad) {  // the fused pass has prepared and evaluated the spectra
-      LASP_CHECK(lasp::launch_cov(g, s, ca, st), "covariance / model Jacobian");
-    } else {
+    if (!out_grad) {  // else the fused pass has evaluated the spectra
       ca.os = os;
       ca.set_status = 1;
       ca.model_out = out_model;
-      LASP_CHECK(lasp::launch_cov_oneshot(g, s, ca, st), "covariance / model Jacobian");
     }
+    LASP_CHECK(apart && !out_grad ? lasp::launch_cov_oneshot(g, s, ca, st)
+                                  : lasp::launch_cov(g, s, ca, st),
+               "covariance / model Jacobian");
   }
+  if (!apart)
+    LASP_CHECK(lasp::launch_outputs(g, s, out_chi2, out_J, out_neff, opts->status, st), "outputs");
   return LASP_OK;
 }
 

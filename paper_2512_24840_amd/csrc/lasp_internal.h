@@ -183,6 +183,9 @@ hipError_t launch_split_basis(const Geometry &g, const State &s, hipStream_t st)
 hipError_t launch_finalize(const Geometry &g, const State &s, const double *box_lo,
                            const double *box_hi, float *out_params, uint32_t *status_out,
                            double *chi2_out, int32_t *steps_out, hipStream_t st);
+// Outputs of a forward evaluation out of the scratch (each may be NULL).
+hipError_t launch_outputs(const Geometry &g, const State &s, double *chi2_out, float *J_out,
+                          int32_t *neff_out, uint32_t *status_out, hipStream_t st);
 hipError_t launch_progress(const Geometry &g, const State &s, int32_t *steps, int32_t *done,
                            hipStream_t st);
 // Evaluation with covariance and/or model Jacobian (s.fp: four rows per
