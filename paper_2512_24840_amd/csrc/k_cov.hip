@@ -231,7 +231,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(2))) void
   double *sW = sX + 128;      // work
   double *sNu = sW + 64;      // mirrored moments
   double *sBd = sNu + 64;     // continuum power series
-  double *sScal = sBd + 32;   // [0] continuum solved, [1] chi2
+  double *sScal = sBd + 32;   // [0] continuum solved, [1] chi2 (FP64 from the pixels up)
   int *sHa = reinterpret_cast<int *>(sScal + 4);        // [kMaxArms]
   float *sCs = reinterpret_cast<float *>(sScal + 8);    // [kMaxArms] chain factor for sigma
   LmState &lm = *reinterpret_cast<LmState *>(sScal + 16);
@@ -508,8 +508,11 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(2))) void
 
     // ---- one pass per pixel: continuum C, residual e, the residual Jacobian
     //      columns ju_t = C dF''/du_t (scaled in place: registers for mu and
-    //      sigma, LDS for u1..u3), and Ju^T W Ju (15), q = Ju^T W e (5) and
-    //      chi2, each lane in FP32, lanes and waves in FP64 --------------------
+    //      sigma, LDS for u1..u3), and Ju^T W Ju (15) and q = Ju^T W e (5),
+    //      each lane in FP32, lanes and waves in FP64.  chi2 twice: as the
+    //      fused pass forms it, for the caller, and in FP64 from the pixels up,
+    //      for the covariance's scale and for the polish, which compares two
+    //      of them to 1e-10 -------------------------------------------------
     const float wsc = MODE == kOneShot ? row.w : s.wscale[spec];
     {
       constexpr int NC = expansion_terms(BLOCK, ND);
@@ -521,6 +524,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(2))) void
 #pragma unroll
       for (int k = 0; k < 20; ++k) acc[k] = 0.f;
       float chi2_part = 0.f, cmin = INFINITY;
+      double chi2_64 = 0.0;
 #pragma unroll
       for (int i = 0; i < kNPL; ++i) {
         const float t = (float)(i - kMid);
@@ -529,8 +533,9 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(2))) void
         for (int k = NC - 2; k >= 0; --k) C = fmaf(C, t, cf[k]);
         const float e = fmaf(-C, f[i], ow[i].x);
         const float we = ow[i].y * e;
-        chi2_part = fmaf(we, e, chi2_part);
+        chi2_64 = fma((double)ow[i].y * (double)e, (double)e, chi2_64);
         if constexpr (MODE != kLm) {
+          chi2_part = fmaf(we, e, chi2_part);
           cmin = fminf(cmin, jb + i < P ? C : INFINITY);
           if (ca.model_out) sF[jb + i] = (C * f[i]) * wsc;
         }
@@ -560,23 +565,30 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(2))) void
         __builtin_amdgcn_sched_barrier(0);
       }
       {
-        const double cs = wave_sum((double)chi2_part);
-        const float cm = wave_min(cmin);
-        if (lane == 0) {
-          sRed[wave * 64 + 0] = cs;
-          sRed[wave * 64 + 1] = (double)cm;
+        const double c64 = wave_sum(chi2_64);
+        if (lane == 0) sRed[wave * 64 + 2] = c64;
+        if constexpr (MODE != kLm) {
+          const double cs = wave_sum((double)chi2_part);
+          const float cm = wave_min(cmin);
+          if (lane == 0) {
+            sRed[wave * 64 + 0] = cs;
+            sRed[wave * 64 + 1] = (double)cm;
+          }
         }
       }
       __syncthreads();
       if (tid == 0) {
-        double cs = 0.0, cm = INFINITY;
+        double c64 = 0.0;
 #pragma unroll
-        for (int w = 0; w < NW; ++w) {
-          cs += sRed[w * 64 + 0];
-          cm = fmin(cm, sRed[w * 64 + 1]);
-        }
-        sScal[1] = cs;
+        for (int w = 0; w < NW; ++w) c64 += sRed[w * 64 + 2];
+        sScal[1] = c64;
         if (MODE != kLm && ca.set_status) {
+          double cs = 0.0, cm = INFINITY;
+#pragma unroll
+          for (int w = 0; w < NW; ++w) {
+            cs += sRed[w * 64 + 0];
+            cm = fmin(cm, sRed[w * 64 + 1]);
+          }
           const int n_eff = MODE == kOneShot ? row.n_eff : s.neff[spec];
           s.chi2[spec] = cs;
           uint32_t st;
