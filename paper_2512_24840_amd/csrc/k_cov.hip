@@ -49,22 +49,39 @@ struct CovLayout {
   int bytes;
 };
 
+// Doubles behind x_off, after the reductions' [nwaves][64]: moments, Ju^T W Ju
+// and q, X and work [D + 1][5], the mirrored moments, the power series,
+// scalars, for D <= 10.
+constexpr int kMomLen = 32, kJJLen = 24, kXLen = 56, kNuLen = 32, kBdLen = 32, kScalLen = 16;
+constexpr int kCovLen = kMomLen + kJJLen + 2 * kXLen + kNuLen + kBdLen + kScalLen;
+// The polish's: its state, then the feature rows [nb][4] as floats.
+constexpr int kLmLen = 68;
+
 // The staged row region (floats [0, k_off)) holds F' rows for the
-// convolutions, then the reductions' scratch and rows on their way out.
-__host__ __device__ inline CovLayout cov_layout(const Geometry &g, int nwaves) {
-  CovLayout L;
+// convolutions, then the reductions' scratch and rows on their way out.  With
+// one arm and margins up to 64, four workgroups of 128 threads share a CU's
+// LDS (covariance of 8,000 x 1,550 px 345 us, 407 with three) and two of 256.
+__host__ __device__ constexpr CovLayout cov_layout(const Geometry &g, int nwaves, bool lm) {
+  CovLayout L{};
   int cols = kOffF + (g.ldF > kNPL * g.block ? g.ldF : kNPL * g.block) + 32;
   L.ks = ((2 * g.M + 1 + 7) & ~7) + 8;
   L.k_off = (cols + 3) & ~3;
   L.d_off = (L.k_off + g.n_arms * 3 * L.ks + 3) & ~3;
   const int fl_end = L.d_off + 3 * kNPL * g.block;
   L.x_off = ((fl_end * 4) + 15) & ~15;
-  // doubles: reduction [nwaves][64], moments [64], JuJu + q [32], X [128],
-  // work [64], mirrored moments [64], power series [32], scalars [16], LM
-  // state [80]; then the feature rows [60][4] as floats
-  L.bytes = L.x_off + 8 * (nwaves * 64 + 64 + 32 + 128 + 64 + 64 + 32 + 16 + 80) + 4 * 4 * kNB * kMaxClasses;
+  L.bytes = L.x_off + 8 * (nwaves * 64 + kCovLen) + (lm ? 8 * kLmLen + 4 * 4 * g.nb : 0);
   return L;
 }
+constexpr int cov_bytes(int block) {
+  Geometry g{};
+  g.M = 64;
+  g.n_arms = 1;
+  g.block = block;
+  g.nb = kNB;
+  return cov_layout(g, block / 64, true).bytes;
+}
+static_assert(4 * cov_bytes(128) <= 160 * 1024 && 2 * cov_bytes(256) <= 160 * 1024,
+              "workgroups that share a CU");
 
 // 5x5 symmetric positive definite solve (Cholesky, FP64); false if not SPD.
 __device__ inline bool chol5(double (&a)[kNP][kNP], double (&x)[kNP]) {
@@ -110,7 +127,8 @@ struct LmState {
   float cur[8], pt[8];          // kept point, evaluated point
   int done, limit;
 };
-static_assert(sizeof(LmState) <= 80 * sizeof(double), "LM state fits its LDS");
+static_assert(sizeof(LmState) <= kLmLen * sizeof(double) && (kCovLen + kLmLen) % 2 == 0,
+              "LM state fits its LDS, the feature rows are 16-byte aligned");
 
 // After the evaluation at pt (chi2 c1, normal equations nS and q1, positive
 // definite if ok): keep or drop the trial step, test for the end, and form the
@@ -220,22 +238,23 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(2))) void
   constexpr int NWIN = kNPL + kTB - 1;
   constexpr int NCOL = kNPL * BLOCK;  // stride of one staged column
   extern __shared__ __align__(16) unsigned char smem[];
-  const CovLayout L = cov_layout(g, NW);
+  const CovLayout L = cov_layout(g, NW, MODE == kLm);
   float *sF = reinterpret_cast<float *>(smem);
   float *sK = sF + L.k_off;
   float *sD = sF + L.d_off;
   double *sRed = reinterpret_cast<double *>(smem + L.x_off);
   double *sMom = sRed + NW * 64;
-  double *sJJ = sMom + 64;    // JuJu packed [15], q [5]
-  double *sX = sJJ + 32;      // [ND][5]
-  double *sW = sX + 128;      // work
-  double *sNu = sW + 64;      // mirrored moments
-  double *sBd = sNu + 64;     // continuum power series
-  double *sScal = sBd + 32;   // [0] continuum solved, [1] chi2 (FP64 from the pixels up)
+  double *sJJ = sMom + kMomLen;   // JuJu packed [15], q [5]
+  double *sX = sJJ + kJJLen;      // [ND][5]
+  double *sW = sX + kXLen;        // work
+  double *sNu = sW + kXLen;       // mirrored moments
+  double *sBd = sNu + kNuLen;     // continuum power series
+  double *sScal = sBd + kBdLen;   // [0] continuum solved, [1] chi2 (FP64 from the pixels up)
   int *sHa = reinterpret_cast<int *>(sScal + 4);        // [kMaxArms]
   float *sCs = reinterpret_cast<float *>(sScal + 8);    // [kMaxArms] chain factor for sigma
-  LmState &lm = *reinterpret_cast<LmState *>(sScal + 16);
-  float4 *sPhi = reinterpret_cast<float4 *>(sScal + 16 + 80);  // [nb]: phi and its derivatives
+  static_assert(NMOM <= kMomLen && kNP * ND <= kXLen && 3 * ND - 2 <= kNuLen, "fits its LDS");
+  LmState &lm = *reinterpret_cast<LmState *>(sScal + kScalLen);
+  float4 *sPhi = reinterpret_cast<float4 *>(sScal + kScalLen + kLmLen);  // [nb]: phi and its derivatives
 
   const int spec = blockIdx.x;
   const int P = g.P, M = g.M;
@@ -779,7 +798,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(2))) void
 
 template <int BLOCK, int ND, int MODE, bool NODES>
 hipError_t launch_cov_k(const Geometry &g, const State &s, const CovArgs &ca, hipStream_t st) {
-  const CovLayout L = cov_layout(g, BLOCK / 64);
+  const CovLayout L = cov_layout(g, BLOCK / 64, MODE == kLm);
   auto k = k_cov<BLOCK, ND, MODE, NODES>;
   hipError_t e =
       hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize, L.bytes);
