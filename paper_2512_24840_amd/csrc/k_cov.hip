@@ -516,6 +516,10 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(2))) void
       int jb = j0;
       opaque(jb);  // the Chebyshev values formed here are not kept for the passes below
       lane_moments<NODES, ND>(jb, P, f, ow, acc);
+      if constexpr (MODE == kLm && !NODES) {  // summed here, not, with every T_k held, where they are stored
+#pragma unroll
+        for (int k = 0; k < NMOM; ++k) opaque(acc[k]);
+      }
       block_sum_lds_f32<NW, NMOM>(acc, sF, sRed, sMom, lane, wave);
     }
     if (wave == 0) {
@@ -711,6 +715,10 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(2))) void
             for (int c = 0; c < NCX; ++c) v[c] = f[i] * column(jb, c, i);
             add(fmaf((float)(jb + i), h, -1.f), v);
           }
+        }
+        if constexpr (MODE == kLm && !NODES) {
+#pragma unroll
+          for (int n = 0; n < NCX * ND; ++n) opaque(acc[n]);
         }
         block_sum_lds_f32<NW, NCX * ND>(acc, sF, sRed, sW, lane, wave);
         if (tid < NCX * ND) sX[(tid % ND) * kNP + t0 + tid / ND] = sW[tid];
