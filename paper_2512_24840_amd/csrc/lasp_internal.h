@@ -692,23 +692,42 @@ __device__ inline RowInfo prepare_row(const float *o_row, const float *i_row, in
     for (int w = 0; w < NW; ++w) t += (int)red[w];
     return __builtin_amdgcn_readfirstlane(t);
   };
+  // f(i) for the thread's pixels, by groups that a short row leaves out (rows
+  // of more than 128 threads have over 2,000 pixels)
+  auto pixels = [&](auto &&f) {
 #pragma unroll
-  for (int i = 0; i < kNPL; ++i) {
+    for (int i = 0; i < 4; ++i) f(i);
+    if (BLOCK > 128 || P > 4 * BLOCK) {
+#pragma unroll
+      for (int i = 4; i < 9; ++i) f(i);
+      if (BLOCK > 128 || P > 9 * BLOCK) {
+#pragma unroll
+        for (int i = 9; i < kNPL; ++i) f(i);
+      }
+    }
+  };
+  if constexpr (BLOCK == 128) {
+#pragma unroll
+    for (int i = 4; i < kNPL; ++i) {
+      o[i] = INFINITY;
+      iv[i] = 0.f;
+    }
+  }
+  pixels([&](int i) {
     const int j = min(tid + i * BLOCK, P - 1);
     o[i] = o_row[j];
     iv[i] = i_row[j];
-  }
+  });
   int n = 0;
   float sum = 0.f, fin = 0.f;  // fin: NaN once a value is not finite
-#pragma unroll
-  for (int i = 0; i < kNPL; ++i) {
+  pixels([&](int i) {
     fin = fmaf(o[i], 0.f, fmaf(iv[i], 0.f, fin));
     const bool ok = isfinite(o[i]) && isfinite(iv[i]) && iv[i] > 0.f && tid + i * BLOCK < P;
     n += ok ? 1 : 0;
     sum += ok ? o[i] : 0.f;
     o[i] = ok ? o[i] : INFINITY;  // above every valid flux in the counts
     iv[i] = ok ? iv[i] : 0.f;
-  }
+  });
   RowInfo r{0, 0, 1.f};
   sum = wave_sum(sum);
   if (lane == 0) scratch[16 + wave] = __float_as_uint(sum);
@@ -742,11 +761,10 @@ __device__ inline RowInfo prepare_row(const float *o_row, const float *i_row, in
       if (b < -100 || b > 100) break;
       const float lo = ldexpf(0.70728f, b), hi = ldexpf(1.41387f, b);
       int c_lo = 0, c_hi = 0;
-#pragma unroll
-      for (int i = 0; i < kNPL; ++i) {
+      pixels([&](int i) {
         c_lo += o[i] < lo ? 1 : 0;
         c_hi += o[i] <= hi ? 1 : 0;
-      }
+      });
       const uint32_t c = (uint32_t)total(c_lo | c_hi << 16);
       if ((c & 0xffffu) <= k0 && k1 < c >> 16) {
         w = exp2f((float)b);
@@ -769,8 +787,7 @@ __device__ inline RowInfo prepare_row(const float *o_row, const float *i_row, in
     for (uint32_t bit = 0x80000000u; bit != 0; bit >>= 1) {
       const uint32_t t = kth | bit;
       int c = 0;
-#pragma unroll
-      for (int i = 0; i < kNPL; ++i) c += __float_as_uint(o[i]) < t ? 1 : 0;
+      pixels([&](int i) { c += __float_as_uint(o[i]) < t ? 1 : 0; });
       if ((uint32_t)total(c) <= k0) kth = t;
     }
     const float v0 = funkey(kth);
