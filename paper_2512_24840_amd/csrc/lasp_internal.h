@@ -667,11 +667,13 @@ struct RowInfo {
 // of their value, show that both order statistics next to the quantile, and
 // with them q, lie inside it; then w = 2^b whatever q is.  b starts from the
 // mean flux and moves by one towards the quantile, which takes one or two
-// counts over registers (four operations per pixel) on a spectrum.  Where
-// the bracket does not close -- order statistics on both sides of an end or
-// within 2^-12 of it, nonpositive or widely scattered fluxes -- q is formed
-// from the order statistics themselves, found bit by bit by the same kind of
-// counts over order-preserving keys.
+// counts over registers (four operations per pixel) on a spectrum.  One count
+// finds nonpositive order statistics, for which w is 1.  Where neither closes
+// -- order statistics on both sides of an end or within 2^-12 of it, widely
+// scattered fluxes -- q is formed from the order statistics themselves, found
+// bit by bit by the same kind of counts over order-preserving keys (objective
+// of 30,000 x 300 px of negative fluxes: 466 us by that search, 271 by the one
+// count).
 //
 // Every thread of the workgroup gets the same RowInfo.  scratch: kPrepScratch
 // words of LDS, free again after a barrier.
@@ -693,7 +695,8 @@ __device__ inline RowInfo prepare_row(const float *o_row, const float *i_row, in
     return __builtin_amdgcn_readfirstlane(t);
   };
   // f(i) for the thread's pixels, by groups that a short row leaves out (rows
-  // of more than 128 threads have over 2,000 pixels)
+  // of more than 128 threads have over 2,000 pixels): covariance of 3,000 x
+  // 300 px 167 -> 158 us, objective of 30,000 x 512 px 304 -> 284
   auto pixels = [&](auto &&f) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) f(i);
@@ -776,6 +779,11 @@ __device__ inline RowInfo prepare_row(const float *o_row, const float *i_row, in
       dir = step;
       b += step;
     }
+  }
+  if (!found) {  // both order statistics nonpositive: so is q, and w stays 1
+    int c = 0;
+    pixels([&](int i) { c += o[i] <= 0.f ? 1 : 0; });
+    found = k1 < (uint32_t)total(c);
   }
   if (!found) {
     // keys in place of the fluxes; the k0-th smallest is the largest value
