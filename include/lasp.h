@@ -154,11 +154,10 @@ extern "C" {
  *  step_graph      1 (default): when no stopping rules, no Clean and one
  *                  emulator class are asked for, lasp_fit_group takes its
  *                  Adam steps with fewer launches: an FP32 group of at most
- *                  1,024 spectra (256 when n_pix + 2 margin > 4,352) in one
- *                  launch, a workgroup per spectrum; BF16X3 groups and
- *                  larger ones up to 4,096 spectra as replays of one HIP
- *                  graph of 25 steps
- *                  (larger groups launch long kernels).  The graph is
+ *                  1,024 spectra (256 when n_pix + 2 margin > 4,352) 250
+ *                  steps a launch, a workgroup per spectrum; BF16X3 groups
+ *                  and larger ones up to 4,096 spectra as replays of one HIP
+ *                  graph of 25 steps (larger groups launch long kernels).  The graph is
  *                  captured on first use and kept with the call's cached
  *                  device scratch until the geometry, the buffers or the
  *                  Adam settings change.  The results are those of
