@@ -257,16 +257,26 @@ inline constexpr MomentNodes kMomentNodes = make_moment_nodes();
 
 // Whether the nodes hold the moments' polynomials (degree n = 2 (nd - 1)) to
 // 1e-7 of their largest value on any lane of a row of P pixels: the Chebyshev
-// interpolation error 2 (a / 2)^7 |p^(7)| / 7!, a = 16 / P, with the seventh
-// derivative of a degree-n polynomial bounded by one, prod_{k < 7} (n^2 - k^2)
-// / (2 k + 1) (Markov).  Degree 10: 1,872 pixels and more, 8: 1,176, 6: 632,
-// 4: 240; shorter rows sum over the pixels.  (Six nodes would serve 3,684
-// pixels and more at degree 10; the step's pass measured 0.290 ms with six,
-// 0.293 with seven and 0.321 with both in one kernel, 16,384 x 3,900.)
+// interpolation error 2 (a / 2)^7 |p^(7)| / 7!, a = 16 / P.  The last lane's
+// nodes reach up to d = 30 / P past the row's end, and there a derivative of a
+// polynomial of degree n bounded by one on the row is at most T_n's: the sum
+// of T_n^(7 + m)(1) d^m / m! with T_n^(k)(1) = prod_{i < k} (n^2 - i^2) /
+// (2 i + 1).  Degree 10: 1,965 pixels and more, 8: 1,229, 6: 656, 4: 242;
+// shorter rows sum over the pixels.  (Six nodes would serve 3,818 pixels and
+// more at degree 10; the step's pass measured 0.290 ms with six, 0.293
+// with seven and 0.321 with both in one kernel, 16,384 x 3,900.)
 inline bool moment_nodes_hold(int nd, int P) {
-  const double n = 2.0 * (nd - 1), a = 16.0 / (double)P;
-  double b = 2.0;
-  for (int k = 0; k < kNodes; ++k) b *= (n * n - (double)k * k) / (2.0 * k + 1.0) / (k + 1.0) * 0.5 * a;
+  const int n = 2 * (nd - 1);
+  const double a = 16.0 / (double)P, d = 30.0 / (double)P;
+  auto step = [&](int k) { return ((double)n * n - (double)k * k) / (2.0 * k + 1.0); };
+  double term = 1.0, b = 0.0;
+  for (int k = 0; k < kNodes; ++k) term *= step(k);
+  for (int k = kNodes; k <= n; ++k) {  // term: T_n^(k)(1) d^m / m!, m = k - 7
+    b += term;
+    term *= step(k) * d / (double)(k - kNodes + 1);
+  }
+  b *= 2.0;
+  for (int k = 0; k < kNodes; ++k) b *= 0.5 * a / (k + 1.0);
   return b <= 1e-7;
 }
 
