@@ -84,7 +84,6 @@ __global__ void k_finalize(Geometry g, State s, double blo0, double blo1, double
   if (steps_out) steps_out[spec] = s.t[spec];
 }
 
-// Steps taken and stopped flag of each slot.
 // The spectra still taking steps, in index order within each Teff regime
 // (with several emulator classes: cool, cool/warm blend, warm, warm/hot
 // blend, hot, from the current parameters), regimes in that order, so that
@@ -150,6 +149,7 @@ __global__ __launch_bounds__(1024) void k_compact(Geometry g, State s, int *orde
   if (t == 1023) *n_active = first[kKeys];
 }
 
+// Steps taken and stopped flag of each slot.
 __global__ void k_progress(Geometry g, State s, int32_t *steps, int32_t *done) {
   const int spec = blockIdx.x * blockDim.x + threadIdx.x;
   if (spec >= g.B) return;

@@ -49,7 +49,8 @@ struct Geometry {
   int P;        // pixels
   int M;        // margin
   int Pe;       // P + 2M basis columns
-  int ldF;      // row stride of F' / F-bar' / padded basis (multiple of 64, >= Pe)
+  int ldF;      // row stride of F' / F-bar' / padded basis (>= Pe; a multiple of 128: the adjoint
+                // contractions and the fit's Phi-bar split it into eight parts of 16-column blocks)
   int nd;       // continuum coefficients D + 1
   int block;    // threads of the fused pass
   int n_arms;   // >= 1
@@ -413,30 +414,6 @@ __device__ inline void adam_update(const AdamCfg &c, const AdamStep &s, float gr
   u = fmaf(-s.step_size, m / denom, u);
 }
 
-// Butterfly reduce-scatter of N per-lane values over a 64-lane wave.
-// On return every lane holds, in v[0], the wave-wide sum of value index
-// lane / (64 / N); lanes with lane % (64 / N) == 0 are the writers.
-template <int N, typename T>
-__device__ inline T wave_reduce_scatter(T (&v)[N], int lane) {
-  static_assert(N >= 1 && N <= 64 && (N & (N - 1)) == 0, "N must be a power of two <= 64");
-  int off = 32;
-#pragma unroll
-  for (int cnt = N; cnt > 1; cnt >>= 1, off >>= 1) {
-    const int half = cnt >> 1;
-    const bool hi = (lane & off) != 0;
-#pragma unroll
-    for (int i = 0; i < half; ++i) {
-      T send = hi ? v[i] : v[half + i];
-      T keep = hi ? v[half + i] : v[i];
-      v[i] = keep + __shfl_xor(send, off, 64);
-    }
-  }
-  T r = v[0];
-  for (; off >= 1; off >>= 1) r += __shfl_xor(r, off, 64);
-  return r;
-}
-
-
 // Makes the compiler treat x as a new value: computations from x after this
 // point are not merged with the same computations before it (which would
 // keep their results live across phases and raise register pressure).
@@ -451,44 +428,6 @@ __device__ inline double read_lane(double v, int l) {
   const int lo = __builtin_amdgcn_readlane((int)b, l);
   const int hi = __builtin_amdgcn_readlane((int)(b >> 32), l);
   return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
-}
-
-
-template <int N>
-struct Pow2 {
-  static constexpr int v = N <= 1 ? 1 : 2 * Pow2<(N + 1) / 2>::v;
-};
-template <>
-struct Pow2<1> {
-  static constexpr int v = 1;
-};
-
-// Sum of NV per-lane doubles over the workgroup, result in out[0..NV).
-// Chunks of 32 go through the wave butterfly, then across waves in a
-// fixed order (deterministic).
-template <int NW, int NV>
-__device__ inline void block_sum_doubles(const double (&acc)[NV], double *red, double *out,
-                                         int lane, int wave) {
-  constexpr int kChunks = (NV + 31) / 32;
-#pragma unroll
-  for (int ch = 0; ch < kChunks; ++ch) {
-    constexpr int kW = NV < 32 ? Pow2<NV>::v : 32;
-    double tmp[kW];
-#pragma unroll
-    for (int i = 0; i < kW; ++i) tmp[i] = (ch * 32 + i < NV) ? acc[(ch * 32 + i) % NV] : 0.0;
-    const double r = wave_reduce_scatter<kW, double>(tmp, lane);
-    constexpr int kStride = 64 / kW;
-    if ((lane % kStride) == 0) red[wave * 64 + lane / kStride] = r;
-    __syncthreads();
-    const int t = threadIdx.x;
-    if (t < kW && ch * 32 + t < NV) {
-      double s = 0.0;
-#pragma unroll
-      for (int w = 0; w < NW; ++w) s += red[w * 64 + t];
-      out[ch * 32 + t] = s;
-    }
-    __syncthreads();
-  }
 }
 
 // Orders a wave's LDS accesses so that lanes see each other's stores.
