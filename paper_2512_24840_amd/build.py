@@ -31,8 +31,8 @@ HIP_FLAGS = [
 # same results bit for bit.  Elsewhere it did not pay (the covariance
 # kernel spills more, the forward contraction ran slower), so it stays off.
 # The covariance kernel's iterating form holds the whole evaluation in a
-# loop: constants and addresses hoisted out of it spill 84 bytes per lane
-# (3,900 px), none with the hoisting off; its other forms do not change.
+# loop: constants and addresses hoisted out of it spill 84 to 116 bytes per
+# lane, at most 20 with the hoisting off; its other forms do not change.
 EXTRA_FLAGS = {
     "k_cov.hip": ["-mllvm", "-disable-machine-licm"],
     "k_fused.hip": ["-mllvm", "-amdgpu-use-amdgpu-trackers=1", "-mllvm", "-amdgpu-sched-strategy=max-ilp"],

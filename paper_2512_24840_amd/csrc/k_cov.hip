@@ -217,16 +217,19 @@ __device__ inline void lm_step(LmState &m, int lane) {
 // X columns fold 17 pixels onto them too), the continuum is a local expansion
 // and chi2 comes from the same pass, so that no fused pass goes before.
 // Measured at 16,384 x 3,900, covariance with its preparation and evaluation:
-// 1.20 ms, against 1.31 + 0.25 + 0.45 ms as three kernels at the start;
-// Jacobian of 509 x 7,800 px in three arms: 0.134 ms against 0.33.
+// 1.13 ms, against 1.31 + 0.25 + 0.45 ms as three kernels; after a fit, with
+// the rows prepared, 1.07.  Jacobian of 509 x 7,800 px in three arms: 0.135
+// ms against 0.33.
 //
-// kLm runs a spectrum's whole iteration in its workgroup: the four F' rows at
-// the trial point are formed here from the basis (in L2) -- the matrix cores'
+// kLm runs a spectrum's whole iteration in its workgroup: the F' rows at the
+// trial point are formed here from the basis (in L2) -- the matrix cores'
 // FP32 products are chains of fused multiply-adds over k in order, and the
 // chain below is the same one bit for bit -- and nothing is launched, counted
-// or waited for between iterations.  A plain fit, at the start with six
-// launches per iteration for all spectra: one of 1,550 px 446 -> 166 us (the
-// kernel 124), 16,384 x 3,900 21.9 -> 7.7 ms.
+// or waited for between iterations.  Row 0 and chi2 come first; the columns
+// follow only where the point is kept and a step from it is still to be made.
+// A plain fit, against six launches per iteration for all spectra: one of
+// 1,550 px 375 -> 163 us (this kernel 126), 16,384 x 3,900 with the
+// covariance 24.4 -> 7.9 ms (8.8 with every trial evaluated in full).
 template <int BLOCK, int ND, int MODE, bool NODES>
 __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(2))) void k_cov(
     Geometry g, State s, CovArgs ca) {

@@ -128,9 +128,9 @@ __host__ __device__ inline FusedLayout fused_layout(const Geometry &g, int nwave
 // written from here.  A prepared (o/w, W w^2) array would be written once
 // and read once, 69.6 KB of the 117 KB that one spectrum then moves, beside a
 // launch of its own.  Measured at 65,536 x 3,900, preparation and pass:
-// 1.78 ms, against 0.80 + 1.45 ms with k_prepare before it.
+// 1.48 ms, against 0.80 + 1.24 ms with k_prepare before it.
 //
-// FIT: all Adam steps of a spectrum in its workgroup, for groups too small to
+// FIT: many Adam steps of a spectrum in its workgroup, for groups too small to
 // fill the chip, whose steps are bound by the latency of three kernels.  F' is
 // formed here from the basis (in L2) and Phi-bar from F-bar' in LDS, by the
 // same chains of fused multiply-adds as the contractions' matrix products, so

@@ -212,8 +212,8 @@ State offset_state(const State &s, const Geometry &g, int slot0, int fp_rows, in
 // one.  Each call pays for it, so a grid first runs through the same bounds
 // on the ratios themselves, drawn in by 1e-15 (rounding of the products here
 // and of the logarithms there stays below that): two products and compares
-// per pixel instead of a logarithm and a division, 1 us instead of 65 us at
-// 3,900 pixels.  What does not pass is left to the rule.
+// per pixel instead of a logarithm and a division, 2.9 us instead of 70 us a
+// call at 3,900 pixels.  What does not pass is left to the rule.
 int check_grid(const double *w, int P, double *dl_out) {
   if (w[0] > 0.0 && isfinite(w[0]) && isfinite(w[P - 1]) && w[P - 1] > w[0]) {
     const double dl = log10(w[P - 1] / w[0]) / (double)(P - 1);

@@ -173,7 +173,7 @@ hipError_t launch_fused(const Geometry &g, const State &s, int adjoint, float *m
 // whole status.
 hipError_t launch_fused_oneshot(const Geometry &g, const State &s, int adjoint, float *model_out,
                                 const OneShot &os, hipStream_t st);
-// n_steps Adam steps of every spectrum, one workgroup each (one emulator
+// n_steps further Adam steps of every spectrum, one workgroup each (one emulator
 // class, FP32 contractions, no stopping rules): the results of as many
 // launches of the three step kernels, bit for bit.
 hipError_t launch_fit(const Geometry &g, const State &s, const AdamCfg &adam, int n_steps,

@@ -1,6 +1,7 @@
 """The one-shot evaluation's fused pass prepares its spectra itself; a grouped
-fit of zero steps prepares them with k_prepare.  At the same parameters both
-give the same chi2 and status bits, and outputs may take the place of u."""
+fit of zero steps prepares them with k_prepare.  At the same parameters (up to
+the rounding of u from its physical values) both give the same chi2 and the
+same status, and outputs may take the place of u."""
 
 import numpy as np
 import pytest

@@ -63,13 +63,11 @@ def test_polish_limit_is_flagged_and_fits_are_isolated():
 
 
 def test_plain_lm_with_200_iterations_alone_equals_in_group():
-    """The plain method (no Adam steps, at most 200 LM iterations): the call
-    stops enqueuing iterations once every spectrum has stopped, so a fit
-    alone ends soon after its own stop while in the group the iterations
-    run on until the slowest spectrum stops -- the results must agree bit
-    for bit (a stopped spectrum's iterations change nothing), sit within a
-    tenth of the fit tolerances of the oracle's LM, and none may reach the
-    iteration limit."""
+    """The plain method (no Adam steps, at most 200 LM iterations): a
+    spectrum's workgroup ends at the spectrum's own stop, beside others that
+    iterate on -- a fit alone must agree with the same fit in the group bit
+    for bit, sit within a tenth of the fit tolerances of the oracle's LM, and
+    none may reach the iteration limit."""
     print("[LM polish] plain LM, 200 iterations: alone == in group, vs the oracle", flush=True)
     shape, basis, batch = problem("lamost1550", 8, 61)
     cfg = oracle.Config.from_shape(shape, BOX_LO, BOX_HI)

@@ -2,7 +2,7 @@
 
 The objective does not depend on the weight, and a power of two leaves every
 rounding where it is, so whatever branch finds it -- the bracket over
-register counts, the select over LDS keys, no weight at all -- the results
+register counts, the search bit by bit, no weight at all -- the results
 equal those of weight 1 bit for bit."""
 
 import numpy as np
@@ -18,7 +18,7 @@ DEV = torch.device("cuda:0")
 
 def _rows(batch):
     """Rows whose quantile the bracket finds, and rows it must leave to the
-    select: order statistics on both sides of 2^(b + 1/2) and right beside
+    bitwise search: order statistics on both sides of 2^(b + 1/2) and right beside
     it, few valid pixels, nonpositive and widely scattered fluxes."""
     obs, ivar = batch.obs.copy(), batch.ivar.copy()
     half = obs.shape[1] // 2

@@ -1,10 +1,10 @@
-"""The Adam steps of lasp_fit_group replayed from the cached HIP graph of
-25 steps (opts.step_graph, the default) against the same steps launched one
-kernel at a time: the same kernels with the same arguments, so every output
-must agree bit for bit -- over chunk counts with and without a remainder,
-replays of one graph across calls with other work between them, argument
-changes that need a new graph, BF16x3, a side stream, and against the
-FP64 oracle."""
+"""opts.step_graph (the default) against the same Adam steps launched one
+kernel at a time: every output must agree bit for bit -- over step counts
+with and without a remainder, across calls with other work between them,
+argument changes, BF16x3, a side stream, and against the FP64 oracle.  FP32
+groups of this size take their steps in one launch; BF16x3 replays the cached
+HIP graph of 25 steps (FP32 groups that take the graph:
+test_gpu_step_graph_groups.py)."""
 
 import sys
 
